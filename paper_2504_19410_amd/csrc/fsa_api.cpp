@@ -180,21 +180,22 @@ fsa_status fsa_plan_create(const fsa_kernel* k, int d, const double* L, const in
         *out = pl;
         return FSA_OK;
     }
-    // twiddle tables: P0 = 2 N0; P1 = 2 N1 (3D); M = N_last; P_last = 2 N_last
+    // twiddle tables: P0 = 2 N0; P1 = 2 N1 (3D); M = N_last; P_last = 2 N_last;
+    // N0, N1 for the unpadded transforms of the derivative
     size_t off = 0;
-    pl->tw_off_p0 = off;
-    off += 2 * N[0];
-    pl->tw_off_p1 = off;
-    if (d == 3) off += 2 * N[1];
-    pl->tw_off_m = off;
-    off += Nl;
-    pl->tw_off_pl = off;
-    off += 2 * Nl;
-    if (pl->n_spectral) {  // unpadded transforms of the derivative on the N-grid
-        pl->tw_off_n0 = off;
-        off += N[0];
-        pl->tw_off_n1 = off;
-        off += N[1];
+    auto table = [&](int64_t n, bool staged) {
+        const size_t at = off;
+        pl->tws[pl->n_tws++] = fsa::TwTables{at, (int)n, staged};
+        off += (size_t)n * (staged ? fsa::kTwTables : 1);
+        return at;
+    };
+    pl->tw_off_p0 = table(2 * N[0], true);
+    if (d == 3) pl->tw_off_p1 = table(2 * N[1], true);
+    pl->tw_off_m = table(Nl, true);
+    pl->tw_off_pl = table(2 * Nl, false);
+    if (pl->n_spectral) {
+        pl->tw_off_n0 = table(N[0], true);
+        pl->tw_off_n1 = table(N[1], true);
     }
     pl->tw_elems = off;
     *out = pl;
@@ -249,19 +250,7 @@ fsa_status fsa_build_tensor(fsa_plan pl, void* stream) {
         pl->built = true;
         return FSA_OK;
     }
-    char* tw = (char*)pl->twiddles;
-    const int64_t Nl = pl->N[pl->d - 1];
-    e = fsa::build_twiddles(pl->prec, (int)(2 * pl->N[0]), tw + pl->tw_off_p0 * pl->csize, st);
-    if (e == hipSuccess && pl->d == 3)
-        e = fsa::build_twiddles(pl->prec, (int)(2 * pl->N[1]), tw + pl->tw_off_p1 * pl->csize, st);
-    if (e == hipSuccess)
-        e = fsa::build_twiddles(pl->prec, (int)Nl, tw + pl->tw_off_m * pl->csize, st);
-    if (e == hipSuccess)
-        e = fsa::build_twiddles(pl->prec, (int)(2 * Nl), tw + pl->tw_off_pl * pl->csize, st);
-    if (e == hipSuccess && pl->n_spectral)
-        e = fsa::build_twiddles(pl->prec, (int)pl->N[0], tw + pl->tw_off_n0 * pl->csize, st);
-    if (e == hipSuccess && pl->n_spectral)
-        e = fsa::build_twiddles(pl->prec, (int)pl->N[1], tw + pl->tw_off_n1 * pl->csize, st);
+    e = fsa::build_twiddles(pl->prec, pl->tws, pl->n_tws, pl->twiddles, st);
     if (e != hipSuccess) return hip_fail(e, "fsa_build_tensor: twiddle kernels");
     e = fsa::build_tensor_device(pl->kp, pl->d, pl->L, pl->N, pl->h, pl->prec, pl->tensor,
                                  &pl->line_order, st);

@@ -21,7 +21,8 @@
 //
 // Every per-thread phase is __host__ __device__ so that the index logic can
 // be emulated thread by thread on the CPU (tests/host).  Twiddles come from
-// a table tw[m] = exp(-2 pi i m / P) built in FP64 on the host.
+// tables built in FP64 (rounded to the transform's precision once): the plain
+// table tw[m] = exp(-2 pi i m / P), or the staged tables (StagedTw).
 #pragma once
 
 #if defined(__HIPCC__)
@@ -412,6 +413,32 @@ constexpr bool fft_alt_distinct(int P) {
     return false;
 }
 
+// The staged twiddle tables of a length P: what the stages of one radix
+// sequence read, in the order they read it.  Stage s >= 1 (NS = R_0 ...
+// R_{s-1}) multiplies operand q = 1 .. R_s - 1 of butterfly j by
+// exp(-2 pi i q k / (NS R_s)), k = j mod NS; its entries lie at
+// off(s) + (q - 1) NS + k with off(s) = NS - R_0 (the stages before it hold
+// NS - R_0 entries).  The plain table gives the same values at index
+// q k P / (NS R_s), where the 64 lanes of one load lie q P / (NS R_s) entries
+// apart and touch up to 64 cache lines; here they are neighbours.
+// A length's tables follow each other: the plain one, then, P entries each,
+// family 0 forward and inverse and family 1 forward and inverse.
+constexpr int kTwTables = 5;
+constexpr int staged_table(int alt, bool inv) { return 1 + 2 * alt + (inv ? 1 : 0); }
+
+// Entry e of the staged table of the radices r[0 .. n-1] (execution order) of
+// length P: the plain table's index of its value, -1 past the last entry.
+FSA_HD constexpr int staged_index(const int* r, int n, int P, int e) {
+    int ns = r[0];
+    for (int s = 1; s < n; ++s) {
+        const int cnt = ns * (r[s] - 1);
+        if (e < cnt) return (e / ns + 1) * (e % ns) * (P / (ns * r[s]));
+        e -= cnt;
+        ns *= r[s];
+    }
+    return -1;
+}
+
 constexpr bool fft_length_supported(long P) {
     if (P < 8 || P > 4096) return false;
     long m = P;
@@ -549,6 +576,52 @@ struct Fft {
             }
             if constexpr (ZH && s == 0) dft_zh<RAD, INV>(&v[b * RAD]);
             else dft<RAD, INV>(&v[b * RAD]);
+        }
+    }
+
+    // ---- staged twiddles (staged_index) --------------------------------------
+    static constexpr int st_off(int s) { return ns(s) - radix(0); }
+    // this transform's staged table, from its length's tables
+    FSA_HD static const C* staged(const C* tw) { return tw + (size_t)staged_table(ALT, INV) * P_; }
+
+    // stage s with twiddles from the staged table
+    template <int s, bool ZH = false>
+    FSA_HD static void compute_st(C (&v)[V], int tid, const C* __restrict__ st) {
+        constexpr int RAD = radix(s), NS = ns(s), NB = nb(s), NBT = nbt(s), OFF = st_off(s);
+#pragma unroll
+        for (int b = 0; b < NBT; ++b) {
+            const int j = tid + b * T;
+            if ((NB % T) != 0 && j >= NB) continue;
+            if constexpr (NS > 1) {
+                const int k = j % NS;
+#pragma unroll
+                for (int q = 1; q < RAD; ++q) {
+                    const C w = st[OFF + (q - 1) * NS + k];
+                    v[b * RAD + q] = INV ? cmulc(v[b * RAD + q], w) : cmul(v[b * RAD + q], w);
+                }
+            }
+            if constexpr (ZH && s == 0) dft_zh<RAD, INV>(&v[b * RAD]);
+            else dft<RAD, INV>(&v[b * RAD]);
+        }
+    }
+
+    // register twiddles (load_tw's layout) from the staged table
+    FSA_HD static void load_tw_st(C (&w)[NTW], int tid, const C* __restrict__ st) {
+        load_tw_st_from<1>(w, tid, st);
+    }
+    template <int s>
+    FSA_HD static void load_tw_st_from(C (&w)[NTW], int tid, const C* __restrict__ st) {
+        if constexpr (s < S) {
+            constexpr int RAD = radix(s), NS = ns(s), NB = nb(s), NBT = nbt(s), OFF = tw_off(s);
+#pragma unroll
+            for (int b = 0; b < NBT; ++b) {
+                const int j = tid + b * T;
+                const int k = ((NB % T) != 0 && j >= NB) ? 0 : j % NS;
+#pragma unroll
+                for (int q = 1; q < RAD; ++q)
+                    w[OFF + b * (RAD - 1) + q - 1] = st[st_off(s) + (q - 1) * NS + k];
+            }
+            load_tw_st_from<s + 1>(w, tid, st);
         }
     }
 
@@ -770,16 +843,6 @@ struct Fft {
     }
 
 #if defined(__HIPCC__)
-    static __device__ __forceinline__ void sync() {
-        if constexpr (T <= 64) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        } else {
-            __syncthreads();
-        }
-    }
-
     // Orders LDS only: waits for this wave's LDS operations, then a wave
     // (T <= 64) or workgroup barrier; global loads in flight keep flying.
     static __device__ __forceinline__ void sync_lds() {
@@ -856,11 +919,11 @@ struct Fft {
 
     template <int s>
     static __device__ __forceinline__ void run_g_from(C (&v)[V], C* scr, int tid,
-                                                      const C* __restrict__ tw) {
+                                                      const C* __restrict__ st) {
         if constexpr (s < S) {
             exchange<s>(v, scr, tid);
-            compute<s>(v, tid, tw);
-            run_g_from<s + 1>(v, scr, tid, tw);
+            compute_st<s>(v, tid, st);
+            run_g_from<s + 1>(v, scr, tid, st);
         }
     }
 
@@ -881,28 +944,28 @@ struct Fft {
 
     template <int s>
     static __device__ __forceinline__ void run_g_split_from(C (&v)[V], R* scr, int tid,
-                                                            const C* __restrict__ tw) {
+                                                            const C* __restrict__ st) {
         if constexpr (s < S) {
             exchange_split<s>(v, scr, tid);
-            compute<s>(v, tid, tw);
-            run_g_split_from<s + 1>(v, scr, tid, tw);
+            compute_st<s>(v, tid, st);
+            run_g_split_from<s + 1>(v, scr, tid, st);
         }
     }
 
     // run_g with every exchange through a real scratch of SCR values
     static __device__ __forceinline__ void run_g_split(C (&v)[V], R* scr, int tid,
-                                                       const C* __restrict__ tw) {
-        compute<0>(v, tid, tw);
-        run_g_split_from<1>(v, scr, tid, tw);
+                                                       const C* __restrict__ st) {
+        compute_st<0>(v, tid, st);
+        run_g_split_from<1>(v, scr, tid, st);
     }
 
-    // twiddles from the (cached) global table, LDS-only synchronisation
+    // twiddles from the (cached) staged table, LDS-only synchronisation
     // (ZH: the upper half of every first-stage operand set is zero)
     template <bool ZH = false>
     static __device__ __forceinline__ void run_g(C (&v)[V], C* scr, int tid,
-                                                 const C* __restrict__ tw) {
-        compute<0, ZH>(v, tid, tw);
-        run_g_from<1>(v, scr, tid, tw);
+                                                 const C* __restrict__ st) {
+        compute_st<0, ZH>(v, tid, st);
+        run_g_from<1>(v, scr, tid, st);
     }
 
     // Whether this thread's twiddles fit a register budget of ~56 VGPRs; the
@@ -917,34 +980,6 @@ struct Fft {
     static __device__ __forceinline__ void run_r(C (&v)[V], C* scr, int tid, const C (&w)[NTW]) {
         compute_r<0, ZH>(v, tid, w);
         run_r_from<1>(v, scr, tid, w);
-    }
-
-    template <int s>
-    static __device__ __forceinline__ void run_from(C (&v)[V], C* scr, int tid,
-                                                    const C* __restrict__ tw) {
-        if constexpr (s < S) {
-            if constexpr (reg_exchange(s)) {
-                swap_bit<0>(v, tid);
-                swap_bit<1>(v, tid);
-                swap_bit<2>(v, tid);
-            } else {
-                store<s - 1>(v, scr, tid);
-                sync();
-                load<s>(v, scr, tid);
-                sync();
-            }
-            compute<s>(v, tid, tw);
-            run_from<s + 1>(v, scr, tid, tw);
-        }
-    }
-
-    // v: first-stage operands on entry, last-stage outputs on exit.  Every
-    // thread of the team must call it (it synchronises the team); on return
-    // the scratch may still be read by other threads until the next sync.
-    static __device__ __forceinline__ void run(C (&v)[V], C* scr, int tid,
-                                               const C* __restrict__ tw) {
-        compute<0>(v, tid, tw);
-        run_from<1>(v, scr, tid, tw);
     }
 #endif
 };

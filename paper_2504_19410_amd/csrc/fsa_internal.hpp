@@ -80,8 +80,18 @@ hipError_t launch_dd_step(const fsa_plan_s* pl, int k, const void* rho, void* ph
 hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, const int64_t* N,
                                const double* h, fsa_precision prec, void* tensor_out,
                                int** line_order, hipStream_t st);
-// tw[m] = exp(-2 pi i m / n), m in [0, n), computed in FP64, stored in prec.
-hipError_t build_twiddles(fsa_precision prec, int n, void* out, hipStream_t st);
+// Twiddle tables of a length n at out + off (elements): the plain one
+// (tw[m] = exp(-2 pi i m / n), m in [0, n)) or, staged, all kTwTables of them
+// (fsa_fft.hpp), computed in FP64, stored in prec; one launch for all lengths,
+// whose tables follow each other in the order given.
+struct TwTables {
+    size_t off;
+    int n;
+    bool staged;
+};
+constexpr int kMaxTwLengths = 6;
+hipError_t build_twiddles(fsa_precision prec, const TwTables* tables, int count, void* out,
+                          hipStream_t st);
 
 // Launch configuration of one pass: compile-time variant (0 default, 1
 // alternate radix family, 2 half-size workgroups, 3 exchanges across lanes,
@@ -260,7 +270,10 @@ struct fsa_plan_s {
     size_t ws2_elems = 0;     // complex elements of the second (3D only)
     size_t ws_bytes = 0;
     size_t tensor_elems = 0;  // octant elements
-    // twiddle tables (elements from the start of `twiddles`)
+    // twiddle tables (elements from the start of `twiddles`): the lengths of
+    // the transforms, and P_last for the real passes' pre- and post-processing
+    fsa::TwTables tws[fsa::kMaxTwLengths] = {};
+    int n_tws = 0;
     size_t tw_off_p0 = 0, tw_off_p1 = 0, tw_off_m = 0, tw_off_pl = 0;
     size_t tw_off_n0 = 0, tw_off_n1 = 0;  // DDI: lengths N_0, N_1 (N_last is tw_off_m)
     size_t tw_elems = 0;

@@ -90,9 +90,23 @@ __device__ __forceinline__ int opaque(int x) {
     asm volatile("" : "+v"(x));
     return x;
 }
+// Staged twiddle tables are read at every stage, at addresses of the lane too;
+// hoisted, they cost the long power-of-two transforms the same way.  There it
+// pays in pass C (FP64 from length 1024, 414 -> 360 us at 512 x
+// 512 x 64 and 97 -> 64 us at 2048^2, and FP32 at 4096, 33.0 -> 30.3 us) and
+// in passes B and D on teams of 8 operands per thread (FP64, 1024: pass D
+// 379 -> 195 us); elsewhere it costs (FP32 pass C at 1024: 134 -> 146 us).
 template <typename R, int P>
 constexpr bool fresh_lane() {
     return (P & (P - 1)) != 0 && (sizeof(R) == 8 || P >= 768);
+}
+template <typename R, class F>
+constexpr bool fresh_lane_t() {
+    return fresh_lane<R, F::P>() || (sizeof(R) == 8 && F::P >= 1024 && F::V <= 8);
+}
+template <typename R, int P>
+constexpr bool fresh_lane_conv() {
+    return fresh_lane<R, P>() || P >= (sizeof(R) == 8 ? 1024 : 4096);
 }
 
 // Whether a transposing tile of WT lines of complex values of `csize` bytes
@@ -193,8 +207,9 @@ __global__ __launch_bounds__((R2c<R, M, VAR>::THREADS)) void k_r2c(
     const int team = team_index<K::T>(), tid0 = threadIdx.x % K::T;
     const int tid = tid0;
     C* scr = lds + team * F::SCR;
+    const C* const st = F::staged(twM);
     C w[F::REG_TW ? F::NTW : 1];
-    if constexpr (F::REG_TW) F::load_tw(w, tid, twM);
+    if constexpr (F::REG_TW) F::load_tw_st(w, tid, st);
     C w2[F::REG_TW ? K::NX : 1];  // post-processing twiddles e^{-i pi k / M}, k = tid + i T
     if constexpr (F::REG_TW) {
 #pragma unroll
@@ -241,7 +256,7 @@ __global__ __launch_bounds__((R2c<R, M, VAR>::THREADS)) void k_r2c(
                 v[b * K::R0 + q] = (q < K::HALF && active) ? pf[b * K::HALF + q] : mk(R(0), R(0));
         if (item + ch.stride < ch.last) prefetch(item + ch.stride);
         if constexpr (F::REG_TW) F::template run_r<true>(v, scr, tid, w);
-        else F::template run_g<true>(v, scr, tid, twM);
+        else F::template run_g<true>(v, scr, tid, st);
         F::store_last(v, tid, M, [&](int k, C z) { scr[F::pad(k)] = z; });
         F::sync_lds();
         C x[K::NX];
@@ -313,8 +328,9 @@ __global__ __launch_bounds__((C2r<R, M, VAR>::THREADS)) void k_c2r(
     const int team = team_index<K::T>(), tid0 = threadIdx.x % K::T;
     const int tid = tid0;
     C* scr = lds + team * F::SCR;
+    const C* const st = F::staged(twM);
     C w[F::REG_TW ? F::NTW : 1];
-    if constexpr (F::REG_TW) F::load_tw(w, tid, twM);
+    if constexpr (F::REG_TW) F::load_tw_st(w, tid, st);
     C w2[F::REG_TW ? F::V : 1];  // e^{-i pi k / M} at this thread's first-stage indices k
     if constexpr (F::REG_TW) F::load_first(w2, tid, M, [&](int k) { return tw2M[k]; });
     const Walk ch =
@@ -375,7 +391,7 @@ __global__ __launch_bounds__((C2r<R, M, VAR>::THREADS)) void k_c2r(
         });
         sync_wg_lds();
         if constexpr (F::REG_TW) F::run_r(v, scr, tid, w);
-        else F::run_g(v, scr, tid, twM);
+        else F::run_g(v, scr, tid, st);
         const int inner = col0 + team;
         if (inner < n_inner) {
             const size_t r0 = ((size_t)outer * n_inner + inner) * M;
@@ -430,8 +446,9 @@ __global__ __launch_bounds__((FwdT<R, P, VAR>::THREADS)) void k_fwd_t(
     const int team = team_index<K::T>(), tid0 = threadIdx.x % K::T;
     const int tid = tid0;
     C* scr = lds + team * F::SCR;
+    const C* const st = F::staged(tw);
     C w[F::REG_TW ? F::NTW : 1];
-    if constexpr (F::REG_TW) F::load_tw(w, tid, tw);
+    if constexpr (F::REG_TW) F::load_tw_st(w, tid, st);
     const Walk ch = walk_of<kWalkChunk>(src.total);
     C pf[K::NBT0 * K::HALF];
     int cur_pf = -1, cur_it = -1;  // job cursors of the prefetch and the item walks
@@ -454,7 +471,7 @@ __global__ __launch_bounds__((FwdT<R, P, VAR>::THREADS)) void k_fwd_t(
     };
     if (ch.first < ch.last) prefetch(ch.first);
     for (int item = ch.first; item < ch.last; item += ch.stride) {
-        const int tid = fresh_lane<R, P>() ? opaque(tid0) : tid0;  // per item: fresh_lane
+        const int tid = fresh_lane_t<R, F>() ? opaque(tid0) : tid0;  // per item: fresh_lane
         int loc;
         const JobT jb = src.get(item, loc, cur_it);
         const int N0 = jb.N0;
@@ -470,7 +487,7 @@ __global__ __launch_bounds__((FwdT<R, P, VAR>::THREADS)) void k_fwd_t(
                 v[b * K::R0 + q] = (q < K::HALF && active) ? pf[b * K::HALF + q] : mk(R(0), R(0));
         if (item + ch.stride < ch.last) prefetch(item + ch.stride);
         if constexpr (F::REG_TW) F::template run_r<true>(v, scr, tid, w);
-        else F::template run_g<true>(v, scr, tid, tw);
+        else F::template run_g<true>(v, scr, tid, st);
         sync_wg_lds();
         F::store_last(v, tid, P, [&](int p1, C c) { lds[p1 * K::TS + team] = c; });
         sync_wg_lds();
@@ -515,8 +532,9 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
     const int team = team_index<K::T>(), tid0 = threadIdx.x % K::T;
     const int tid = tid0;
     C* scr = lds + team * F::SCR;
+    const C* const st = F::staged(tw);
     C w[F::REG_TW ? F::NTW : 1];
-    if constexpr (F::REG_TW) F::load_tw(w, tid, tw);
+    if constexpr (F::REG_TW) F::load_tw_st(w, tid, st);
     const Walk ch = walk_of<kWalkChunk>(src.total);
     C tp[K::PREFETCH ? K::NT : 1];
     auto tile_elem = [&](const JobT& jb, int p2, int col0, int e) {
@@ -539,7 +557,7 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
         if (ch.first < ch.last) prefetch(ch.first);
     }
     for (int item = ch.first; item < ch.last; item += ch.stride) {
-        const int tid = fresh_lane<R, P>() ? opaque(tid0) : tid0;  // per item: fresh_lane
+        const int tid = fresh_lane_t<R, F>() ? opaque(tid0) : tid0;  // per item: fresh_lane
         int loc;
         const JobT jb = src.get(item, loc, cur_it);
         const int N0 = jb.N0;
@@ -567,7 +585,7 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
         F::load_first(v, tid, P, [&](int p1) { return lds[p1 * K::TS + team]; });
         sync_wg_lds();
         if constexpr (F::REG_TW) F::run_r(v, scr, tid, w);
-        else F::run_g(v, scr, tid, tw);
+        else F::run_g(v, scr, tid, st);
         const int i0 = col0 + team;
         if (i0 < N0) {
             C* dst = (C*)jb.out + ((size_t)i0 * jb.H + p2) * N1;
@@ -653,10 +671,12 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
     // (the 256-thread conv workgroups can spend up to ~64 VGPRs on them)
     constexpr bool REG = K::SHARED_TW ? Ff::reg_tw(64)
                                       : (Ff::NTW + Fi::NTW) * (int)(sizeof(C) / 4) <= 64;
+    const C* const stf = Ff::staged(tw);
+    const C* const sti = K::SHARED_TW ? stf : Fi::staged(tw);  // one table if palindromic
     C wf[REG ? Ff::NTW : 1];
-    if constexpr (REG) Ff::load_tw(wf, tid, tw);
+    if constexpr (REG) Ff::load_tw_st(wf, tid, stf);
     C wi[(REG && !K::SHARED_TW) ? Fi::NTW : 1];
-    if constexpr (REG && !K::SHARED_TW) Fi::load_tw(wi, tid, tw);
+    if constexpr (REG && !K::SHARED_TW) Fi::load_tw_st(wi, tid, sti);
 
     const int total = src.total;
     const int slots = gridDim.x * K::TPW;
@@ -702,7 +722,7 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
     };
     if constexpr (K::PREFETCH) prefetch(first);
     for (int it = 0; it < chunk; ++it) {
-        const int tid = fresh_lane<R, P>() ? opaque(tid0) : tid0;  // per item: fresh_lane
+        const int tid = fresh_lane_conv<R, P>() ? opaque(tid0) : tid0;  // per item: fresh_lane
         const int item = first + it;
         const bool active = item < total;
         int loc;
@@ -759,13 +779,13 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
                 Ff::template compute_r<1>(v, tid, wf);
                 Ff::template run_r_from<2>(v, scr, tid, wf);
             } else {
-                Ff::template compute<1>(v, tid, tw);
-                Ff::template run_g_from<2>(v, scr, tid, tw);
+                Ff::template compute_st<1>(v, tid, stf);
+                Ff::template run_g_from<2>(v, scr, tid, stf);
             }
         } else if constexpr (REG) {
             Ff::template run_r<true>(v, scr, tid, wf);
         } else {
-            Ff::template run_g<true>(v, scr, tid, tw);
+            Ff::template run_g<true>(v, scr, tid, stf);
         }
         {
             int i = 0;
@@ -773,7 +793,7 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
         }
         if constexpr (REG && K::SHARED_TW) Fi::run_r(v, scr, tid, wf);
         else if constexpr (REG) Fi::run_r(v, scr, tid, wi);
-        else Fi::run_g(v, scr, tid, tw);
+        else Fi::run_g(v, scr, tid, sti);
         if (active) {
             C* pen = (C*)jb.data + (size_t)qp * N0;
             Fi::store_last(v, tid, N0, [&](int i, C c) { pen[i] = c; });

@@ -100,6 +100,8 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec(const void* in,
     __shared__ C lds[K::LDS];
     C* const tile = lds;  // [t][w], also the teams' scratch while they transform
     const int team = team_index<K::T>(), tid = threadIdx.x % K::T;
+    const C* const stf = Ff::staged(tw);
+    const C* const sti = Fi::staged(tw);
     const int ntu = (ln.n_u + K::WT - 1) / K::WT;
     const int tu = blockIdx.x % ntu, v = blockIdx.x / ntu;
     const long base = (long)tu * K::WT * ln.u_stride + (long)v * ln.v_stride;
@@ -119,7 +121,7 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec(const void* in,
             Ff::load_first(x, tid, P, [&](int t) {
                 return act ? mk(((const R*)in)[rb + t], R(0)) : mk(R(0), R(0));
             });
-            Ff::run_g(x, sc, tid, tw);
+            Ff::run_g(x, sc, tid, stf);
             if (act)
                 Ff::store_last(x, tid, P, [&](int t, C c) {
                     if (t < H) ((C*)out)[ro + t] = c;
@@ -130,7 +132,7 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec(const void* in,
                 if (!act) return mk(R(0), R(0));
                 return t < H ? ((const C*)in)[rb + t] : conj(((const C*)in)[rb + P - t]);
             });
-            Fi::run_g(x, sc, tid, tw);
+            Fi::run_g(x, sc, tid, sti);
             if (act) Fi::store_last(x, tid, P, [&](int t, C c) { ((R*)out)[ro + t] = c.x; });
         }
         return;
@@ -166,11 +168,11 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec(const void* in,
     C* sc = lds + team * Ff::SCR;
     // every team has finished with its scratch before the tile is rewritten
     if constexpr (KIND == COL_FWD) {
-        Ff::run_g(x, sc, tid, tw);
+        Ff::run_g(x, sc, tid, stf);
         __syncthreads();
         Ff::store_last(x, tid, P, [&](int t, C c) { tile[t * K::TS + team] = c; });
     } else if constexpr (KIND == COL_MUL) {
-        Ff::run_g(x, sc, tid, tw);
+        Ff::run_g(x, sc, tid, stf);
         // line (u = i2, v = i1) along axis 0; the register holds output i0.
         // g = (f(k) + f(k~)) / 2 with f = a k0^2 + b k0 + c along the line
         const int i2 = tu * K::WT + team, i1 = v;
@@ -189,11 +191,11 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec(const void* in,
             const double k0 = mul.c[0] * qv(i0, mul.N[0]), p0 = mul.c[0] * qp(i0, mul.N[0]);
             c = scale(c, (R)(ha * (k0 * k0 + p0 * p0) + hb * k0 + hbp * p0 + hc));
         });
-        Fi::run_g(x, sc, tid, tw);
+        Fi::run_g(x, sc, tid, sti);
         __syncthreads();
         Fi::store_last(x, tid, P, [&](int t, C c) { tile[t * K::TS + team] = c; });
     } else {
-        Fi::run_g(x, sc, tid, tw);
+        Fi::run_g(x, sc, tid, sti);
         __syncthreads();
         Fi::store_last(x, tid, P, [&](int t, C c) { tile[t * K::TS + team] = c; });
     }

@@ -602,7 +602,7 @@ __global__ __launch_bounds__(Dct<P>::THREADS) void k_dct(const double* __restric
         return mk(tile[t * K::TS + 2 * team], tile[t * K::TS + 2 * team + 1]);
     });
     __syncthreads();
-    F::run_g_split(z, scr + team * F::SCR, tid, tw);
+    F::run_g_split(z, scr + team * F::SCR, tid, F::staged(tw));
     __syncthreads();
     F::store_last(z, tid, K::D, [&](int p, C c) {
         tile[p * K::TS + 2 * team] = c.x;
@@ -779,25 +779,64 @@ hipError_t build_w_table(const KernelParams& kp, int d, const double* L, const i
     return hipGetLastError();
 }
 
+// One length's tables: the plain one, then the staged ones of both radix
+// families and directions (fsa_fft.hpp, kTwTables).
+struct TwLength {
+    int off, n, tables;         // first entry; length; 1 (plain only) or kTwTables
+    int stages[2], r[2][8];     // radices of each family, forward order
+};
+struct TwLengths {
+    TwLength len[kMaxTwLengths];
+    int count, total;
+};
+
 template <typename R>
-__global__ void k_twiddle(cpx<R>* __restrict__ tw, int n) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m < n) {
-        double s, c;
-        sincospi(2.0 * (double)m / (double)n, &s, &c);
-        tw[m] = mk<R>((R)c, (R)-s);
+__global__ void k_twiddle(cpx<R>* __restrict__ tw, TwLengths all) {
+    int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= all.total) return;
+    cpx<R>* const at = tw + e;
+    int i = 0;
+    while (i + 1 < all.count && e >= all.len[i + 1].off) ++i;
+    const TwLength& l = all.len[i];
+    e -= l.off;
+    const int table = e / l.n;
+    int m = e - table * l.n;
+    if (table > 0) {
+        const int alt = (table - 1) / 2, ns = l.stages[alt];
+        const bool inv = (table - 1) % 2 != 0;
+        int r[8];
+        for (int s = 0; s < 8; ++s) r[s] = s < ns ? l.r[alt][inv ? ns - 1 - s : s] : 1;
+        m = staged_index(r, ns, l.n, m);
+        if (m < 0) return;
     }
+    double s, c;
+    sincospi(2.0 * (double)m / (double)l.n, &s, &c);
+    *at = mk<R>((R)c, (R)-s);
 }
 
 }  // namespace
 
-hipError_t build_twiddles(fsa_precision prec, int n, void* out, hipStream_t st) {
-    const int block = 256, grid = (n + block - 1) / block;
-    if (prec == FSA_F32)
-        hipLaunchKernelGGL(k_twiddle<float>, dim3(grid), dim3(block), 0, st, (cpx<float>*)out, n);
-    else
-        hipLaunchKernelGGL(k_twiddle<double>, dim3(grid), dim3(block), 0, st, (cpx<double>*)out, n);
-    return hipGetLastError();
+hipError_t build_twiddles(fsa_precision prec, const TwTables* tables, int count, void* out,
+                          hipStream_t st) {
+    TwLengths all{};
+    if (count < 1 || count > kMaxTwLengths) return hipErrorInvalidValue;
+    all.count = count;
+    for (int i = 0; i < count; ++i) {
+        TwLength& l = all.len[i];
+        l.off = (int)tables[i].off;
+        l.n = tables[i].n;
+        l.tables = tables[i].staged ? kTwTables : 1;
+        for (int alt = 0; alt < 2; ++alt) {
+            const FftPlan p = make_fft_plan(l.n, alt);
+            l.stages[alt] = p.n;
+            for (int s = 0; s < p.n; ++s) l.r[alt][s] = p.r[s];
+        }
+        all.total = l.off + l.n * l.tables;
+    }
+    const dim3 block(256), grid((unsigned)((all.total + 255) / 256));
+    return prec == FSA_F32
+               ? launch_kernel(k_twiddle<float>, grid, block, 0, st, (cpx<float>*)out, all)
+               : launch_kernel(k_twiddle<double>, grid, block, 0, st, (cpx<double>*)out, all);
 }
 
 hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, const int64_t* N,
@@ -806,8 +845,6 @@ hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, c
     // octant extents D_j = N_j + 1, axis 0 innermost; a 2D plan has D2 = 1
     const long D0 = N[0] + 1, D1 = N[1] + 1, D2 = d == 3 ? N[2] + 1 : 1;
     const long n = D0 * D1 * D2;
-    int maxN = 0;
-    for (int j = 0; j < d; ++j) maxN = (int)N[j] > maxN ? (int)N[j] : maxN;
     // the general construction's W table first (the last axis reads it)
     WTable wt{nullptr, 0.0, 0};
     std::vector<void*> wbufs;
@@ -817,7 +854,15 @@ hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, c
     void* tw = nullptr;
     if (e == hipSuccess) e = hipMallocAsync((void**)&a, sizeof(double) * n, st);
     if (e == hipSuccess && d == 3) e = hipMallocAsync((void**)&b, sizeof(double) * n, st);
-    if (e == hipSuccess) e = hipMallocAsync(&tw, 2 * sizeof(double) * 2 * maxN, st);
+    // twiddles of every axis
+    TwTables tws[3] = {};
+    size_t tw_n = 0;
+    for (int j = 0; j < d; ++j) {
+        tws[j] = TwTables{tw_n, (int)(2 * N[j]), true};
+        tw_n += (size_t)kTwTables * 2 * N[j];
+    }
+    if (e == hipSuccess) e = hipMallocAsync(&tw, sizeof(cpx<double>) * tw_n, st);
+    if (e == hipSuccess) e = build_twiddles(FSA_F64, tws, d, tw, st);
     DctEnds ends{};
     ends.kp = kp;
     double prodP = 1.0;
@@ -881,24 +926,23 @@ hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, c
     // contiguous rows
     for (int step = 0; step < d && e == hipSuccess; ++step) {
         const int ax = d - 1 - step;
-        e = build_twiddles(FSA_F64, (int)(2 * N[ax]), tw, st);
-        if (e != hipSuccess) break;
+        const void* atw = (const cpx<double>*)tw + tws[ax].off;
         const Lines ln = lines(ax);
         const int nn = (int)N[ax];
         const double* last_in = d == 3 ? b : a;
         if (step == 0)
-            e = t1_tab ? dct_axis<DctStage::FIRST, double, true>(nullptr, a, ln, nn, tw, ends, st)
-                       : dct_axis<DctStage::FIRST, double, false>(nullptr, a, ln, nn, tw, ends, st);
+            e = t1_tab ? dct_axis<DctStage::FIRST, double, true>(nullptr, a, ln, nn, atw, ends, st)
+                       : dct_axis<DctStage::FIRST, double, false>(nullptr, a, ln, nn, atw, ends, st);
         else if (step < d - 1)
-            e = dct_axis<DctStage::MID, double, false>(a, b, ln, nn, tw, ends, st);
+            e = dct_axis<DctStage::MID, double, false>(a, b, ln, nn, atw, ends, st);
         else if (prec == FSA_F32)
-            e = rows    ? dct_axis<DctStage::LAST, float, true, true>(last_in, nullptr, ln, nn, tw, ends, st)
-                : w_tab ? dct_axis<DctStage::LAST, float, true>(last_in, nullptr, ln, nn, tw, ends, st)
-                        : dct_axis<DctStage::LAST, float, false>(last_in, nullptr, ln, nn, tw, ends, st);
+            e = rows    ? dct_axis<DctStage::LAST, float, true, true>(last_in, nullptr, ln, nn, atw, ends, st)
+                : w_tab ? dct_axis<DctStage::LAST, float, true>(last_in, nullptr, ln, nn, atw, ends, st)
+                        : dct_axis<DctStage::LAST, float, false>(last_in, nullptr, ln, nn, atw, ends, st);
         else
-            e = rows    ? dct_axis<DctStage::LAST, double, true, true>(last_in, nullptr, ln, nn, tw, ends, st)
-                : w_tab ? dct_axis<DctStage::LAST, double, true>(last_in, nullptr, ln, nn, tw, ends, st)
-                        : dct_axis<DctStage::LAST, double, false>(last_in, nullptr, ln, nn, tw, ends, st);
+            e = rows    ? dct_axis<DctStage::LAST, double, true, true>(last_in, nullptr, ln, nn, atw, ends, st)
+                : w_tab ? dct_axis<DctStage::LAST, double, true>(last_in, nullptr, ln, nn, atw, ends, st)
+                        : dct_axis<DctStage::LAST, double, false>(last_in, nullptr, ln, nn, atw, ends, st);
     }
     if (t1_tab) (void)hipFreeAsync(t1_tab, st);
     if (w_tab) (void)hipFreeAsync(w_tab, st);
