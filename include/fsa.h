@@ -289,7 +289,9 @@ typedef enum {
  *      a matrix product on the matrix cores (FP32 MFMA; length 512).
  * and its persistent grid may use `occupancy` resident workgroups per CU
  * (0 = as many as fit).  The library keeps one process-wide table of
- * choices; untuned entries use variant 0 at full occupancy.  fsa_apply,
+ * choices; untuned entries use variant 0 at full occupancy, or variant 1 at
+ * the (precision, pass, length) where it is the faster one on every grid timed
+ * (fsa_tune_get reports it).  fsa_apply,
  * fsa_apply_batched and the server read the table when they launch.  All
  * variants compute the same transform; results differ only by rounding.
  * On first use the table is loaded from the JSON file named by the
@@ -352,7 +354,7 @@ fsa_status fsa_tune_variants(int precision, int pass, int length, int* mask);
  * architecture or names a variant that does not exist (FSA_EINVAL). */
 fsa_status fsa_tune_save(const char* path);
 fsa_status fsa_tune_load(const char* path);
-/* Forgets every entry (all passes back to variant 0, full occupancy). */
+/* Forgets every entry (all passes back to their untuned choice). */
 fsa_status fsa_tune_reset(void);
 
 /* ------------------------------------------------------------------------- */

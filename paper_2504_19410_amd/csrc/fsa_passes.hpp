@@ -116,7 +116,11 @@ constexpr bool fresh_lane_conv() {
 // walk (292 -> 354 us, every workgroup of an XCD reading the same lines at
 // once) and takes the pair walk instead: fetches 2.3 -> 1.09 x the
 // algorithmic bytes at the same time (the Infinity Cache had served the
-// re-reads).  The other transposing passes keep their chunks.
+// re-reads).  Pass B writes such rows and takes the XCD walk, under which one L2
+// merges the parts of a line (FP32, 384^3: 400 -> 360 us; 512 x 512 x 64:
+// 100 -> 90 us).  Pass D reads them: from length 1536 it takes the pair walk
+// (FP32, 128 x 1024 x 64: 104 -> 78 us), below that chunks are faster (384^3:
+// 333 us against 352 in pairs and 416 in XCD order).
 constexpr bool narrow_rows(int wt, int csize) { return wt * csize < 128; }
 
 // This workgroup's walk over `items` items of the launch.
@@ -449,7 +453,8 @@ __global__ __launch_bounds__((FwdT<R, P, VAR>::THREADS)) void k_fwd_t(
     const C* const st = F::staged(tw);
     C w[F::REG_TW ? F::NTW : 1];
     if constexpr (F::REG_TW) F::load_tw_st(w, tid, st);
-    const Walk ch = walk_of<kWalkChunk>(src.total);
+    const Walk ch =
+        walk_of<narrow_rows(K::WT, (int)sizeof(C)) ? kWalkXcd : kWalkChunk>(src.total);
     C pf[K::NBT0 * K::HALF];
     int cur_pf = -1, cur_it = -1;  // job cursors of the prefetch and the item walks
     auto prefetch = [&](int item) {
@@ -535,7 +540,8 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
     const C* const st = F::staged(tw);
     C w[F::REG_TW ? F::NTW : 1];
     if constexpr (F::REG_TW) F::load_tw_st(w, tid, st);
-    const Walk ch = walk_of<kWalkChunk>(src.total);
+    const Walk ch =
+        walk_of<narrow_rows(K::WT, (int)sizeof(C)) && P >= 1536 ? kWalkPair : kWalkChunk>(src.total);
     C tp[K::PREFETCH ? K::NT : 1];
     auto tile_elem = [&](const JobT& jb, int p2, int col0, int e) {
         const int p1 = e / K::WT, ww = e - p1 * K::WT;
@@ -607,10 +613,20 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
 // and items are ordered so that the mirror pencils p1 and P1 - p1, which read
 // the same tensor row, follow each other.
 // ---------------------------------------------------------------------------
+// Radix family of pass C: at length 256 in FP32 variant 0 is 16 x 16 (one
+// exchange through the LDS) and variant 1 is 8 x 4 x 8 (two); 19.4 against 23.5
+// us at 128^3, 32.4 against 39.4 at 128 x 128 x 256, equal at 128 x 1024 x 64.
+// In FP64 16 operands per thread cost what the exchange saves.
+template <typename R, int P>
+constexpr int conv_alt(int var) {
+    return sizeof(R) == 4 && P == 256 ? 1 - var_alt(var) : var_alt(var);
+}
+
 template <typename R, int P, int VAR = 0>
 struct Conv {
-    using Ff = Fft<R, P, false, var_alt(VAR), var_xch(VAR)>;
-    using Fi = Fft<R, P, true, var_alt(VAR), var_xch(VAR)>;
+    static constexpr int ALT = conv_alt<R, P>(VAR);
+    using Ff = Fft<R, P, false, ALT, var_xch(VAR)>;
+    using Fi = Fft<R, P, true, ALT, var_xch(VAR)>;
     using C = cpx<R>;
     static constexpr int T = Ff::T;
     static constexpr int TPW = cmax(1, var_cap(VAR, 256) / T);  // teams per workgroup

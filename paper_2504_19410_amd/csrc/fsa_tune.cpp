@@ -329,6 +329,36 @@ bool nearest(int prec, int key_pass, int len, int cls, Choice* out) {
 }
 }  // namespace
 
+// The variant of an untuned (precision, pass, length): 0, except where the
+// other radix family is faster on every grid that was timed (us, variant 0 /
+// variant 1).  The lines a launch runs do not enter, so that a batch of untuned
+// problems computes bitwise what each computes alone.
+//   Teams of 8 operands per thread fill wider workgroups: in passes B and D
+// whole tiles of 1024 threads; in the real passes one FP64 row of 1024 no
+// longer spills (256 VGPRs and 324 bytes of scratch -> 212 VGPRs).
+//   At 768 the narrower team of family 1 (64 threads of 16 operands) doubles
+// the lines per tile, i.e. the bytes per row that passes B and D write and read.
+//   Pass C at 128 in FP32: family 1 is 16 x 8, one exchange through the LDS
+// less.
+int default_variant(fsa_precision prec, Pass pass, int len) {
+    const bool f32 = prec == FSA_F32;
+    switch (pass) {
+    case Pass::R2C: return !f32 && len == 1024;  // 31.3 / 20.8 (1024^2)
+    case Pass::FWD_T:
+        return len == 768                             // FP32 763 / 398, FP64 402 / 322 (384^3)
+               || (f32 && (len == 1024 || len == 2048));  // 130 / 101 (512 x 512 x 64), 85 / 70
+    case Pass::CONV: return f32 && len == 128;  // 22.8 / 19.6 (64 x 64 x 512)
+    case Pass::INV_T:
+        return len == 768                             // FP32 488 / 336, FP64 354 / 292 (384^3)
+               || (f32 ? len == 2048                  // 104 / 96 (128 x 1024 x 64)
+                       : len == 1024);                // 261 / 195 (512 x 512 x 64)
+    case Pass::C2R:
+        return f32 ? len == 384                       // 184 / 155 (384^3)
+                   : len == 1024 || len == 2048;      // 16.0 / 10.2 (1024^2), 59.5 / 40.6
+    }
+    return 0;
+}
+
 Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched) {
     load_env_once();
     const int cls = size_class(lines);
@@ -336,7 +366,8 @@ Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched) {
     Choice best;
     // a batched launch prefers the batched entries, then the single ones
     if (batched && nearest((int)prec, (int)pass | FSA_PASS_BATCHED, len, cls, &best)) return best;
-    nearest((int)prec, (int)pass, len, cls, &best);
+    if (!nearest((int)prec, (int)pass, len, cls, &best))
+        best.var = default_variant(prec, pass, len);
     return best;
 }
 
