@@ -167,7 +167,7 @@ fsa_status fsa_plan_create(const fsa_kernel* k, int d, const double* L, const in
         // the derivative fits the first array, H > N_1)
         pl->ws2_elems = pl->n_spectral ? (size_t)N[0] * N[1] / 2 : 0;
     }
-    if (p == FSA_DD) {  // the whole padded complex spectrum
+    if (p == FSA_DD) {  // room for the whole padded complex spectrum
         pl->ws1_elems = 1;
         for (int j = 0; j < d; ++j) pl->ws1_elems *= (size_t)(2 * N[j]);
         pl->ws2_elems = 0;

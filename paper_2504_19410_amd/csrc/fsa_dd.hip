@@ -14,9 +14,14 @@
 //           the last to axis 1, the fused forward FFT x T^ x inverse FFT
 //           along axis 0, inverse FFTs back; input zero padding and output
 //           crop folded into the loads and stores.
-// Unlike the FP32/FP64 path it keeps the whole complex padded spectrum
-// (prod P_j values of 32 bytes) and transforms one line per workgroup with a
-// radix-4 FFT in LDS: this mode is about accuracy, not bandwidth.
+// rho and phi are real, so the last axis keeps only its bins 0 .. N_last (the
+// others are conjugates), and its transforms take two rows in one complex FFT.
+// A workgroup of 256 threads transforms W = 1024 / P lines (at least one) with a
+// radix-4 FFT in LDS, neighbouring lines side by side: every wave is full and
+// the strided axes are read in runs of W values.  The arithmetic bounds it (a
+// double-double addition is 20 FP64 operations, a product 10): 64^3 took 342 us
+// on the whole complex spectrum with one line per workgroup of P / 4 threads
+// (half a wave at P = 128), 159 us this way; its fused pass 186 us, now 81.
 // Arrays of reals are interleaved (hi, lo) pairs; complex values are
 // (re.hi, re.lo, im.hi, im.lo).
 #include <hip/hip_runtime.h>
@@ -41,8 +46,9 @@ __device__ __forceinline__ cdd cconj(cdd a) { return cdd{a.re, -a.im}; }
 
 constexpr int kDDThreads = 256;
 constexpr int kDDMaxP = 2048;
-// threads per line: one per radix-4 butterfly, at most kDDThreads
-constexpr int dd_threads(int P) { return P / 4 < 1 ? 1 : P / 4 < kDDThreads ? P / 4 : kDDThreads; }
+// lines per workgroup: one radix-4 butterfly per thread and step, where the line
+// is short enough
+constexpr int dd_lines(int P) { return P >= 4 * kDDThreads ? 1 : 4 * kDDThreads / P; }
 
 // tw[m] = exp(-2 pi i m / P), m < P/2
 __global__ void k_dd_twiddle(cdd* __restrict__ tw, int P) {
@@ -130,47 +136,73 @@ __global__ void k_dd_finalize(const dd* __restrict__ dct, dd* __restrict__ out, 
 }
 
 // ---------------------------------------------------------------------------
-// Evaluation: one line per workgroup, radix-4 steps in LDS.
+// Evaluation: W lines per workgroup, radix-4 steps in LDS.
 // ---------------------------------------------------------------------------
 
-// In-place decimation in time on x[0, P) (bit-reversed order in, natural
-// order out); tw[m] = exp(-2 pi i m / P), m < P/2.  The radix-2 stages run in
+// The W lines of a workgroup in LDS, real and imaginary parts apart (a wave's
+// 16-byte accesses are neighbours): value t of line w at w P + t.
+struct DDTile {
+    dd *re, *im;
+    __device__ __forceinline__ cdd get(int i) const { return cdd{re[i], im[i]}; }
+    __device__ __forceinline__ void put(int i, cdd v) const {
+        re[i] = v.re;
+        im[i] = v.im;
+    }
+};
+
+// In-place decimation in time on every line x[w P, (w + 1) P) (bit-reversed
+// order in, natural order out); tw[m] = exp(-2 pi i m / P), m < P/2.  The
+// radix-2 stages run in
 // pairs (len/2, len) as one radix-4 step per group of four points, with one
 // exchange through LDS per pair, after a leading radix-2 stage when log2 P is
-// odd: points i0, i0 + q, i0 + 2q, i0 + 3q (q = len/4, j = i0 mod len < q)
+// odd or a radix-4 step without twiddles when it is even: points i0, i0 + q, i0 + 2q, i0 + 3q (q = len/4, j = i0 mod len < q)
 // take the len/2 stage's twiddle w_len^(2j) on the odd points of each half,
 // then the len stage's w_len^j on the second half, times -i (forward) or +i
 // (inverse) for the upper pair.
 template <bool INV>
-__device__ void dd_fft_lds(cdd* x, int P, int logP, const cdd* __restrict__ tw) {
+__device__ void dd_fft_lds(const DDTile& x, int W, int P, int logP, const cdd* __restrict__ tw) {
     int len = 4;
     if (logP & 1) {
-        for (int b = threadIdx.x; b < P / 2; b += blockDim.x) {
-            const cdd u = x[2 * b], v = x[2 * b + 1];
-            x[2 * b] = cadd(u, v);
-            x[2 * b + 1] = csub(u, v);
+        for (int b = threadIdx.x; b < W * (P / 2); b += kDDThreads) {
+            const cdd u = x.get(2 * b), v = x.get(2 * b + 1);
+            x.put(2 * b, cadd(u, v));
+            x.put(2 * b + 1, csub(u, v));
         }
         __syncthreads();
         len = 8;
+    } else {  // groups of four points: every twiddle is 1
+        for (int b = threadIdx.x; b < W * (P / 4); b += kDDThreads) {
+            const cdd a0 = x.get(4 * b), a1 = x.get(4 * b + 1);
+            const cdd a2 = x.get(4 * b + 2), a3 = x.get(4 * b + 3);
+            const cdd b0 = cadd(a0, a1), b1 = csub(a0, a1);
+            const cdd b2 = cadd(a2, a3), u3 = csub(a2, a3);
+            const cdd t3 = INV ? cdd{-u3.im, u3.re} : cdd{u3.im, -u3.re};
+            x.put(4 * b, cadd(b0, b2));
+            x.put(4 * b + 2, csub(b0, b2));
+            x.put(4 * b + 1, cadd(b1, t3));
+            x.put(4 * b + 3, csub(b1, t3));
+        }
+        __syncthreads();
+        len = 16;
     }
-    for (; len <= P; len <<= 2) {
-        const int q = len >> 2, step = P / len;
-        for (int b = threadIdx.x; b < P / 4; b += blockDim.x) {
-            const int g = b / q, j = b - g * q;
+    for (int lq = (logP & 1) ? 1 : 2; len <= P; len <<= 2, lq += 2) {
+        const int q = len >> 2, step = P / len;  // q = 2^lq divides P / 4
+        for (int b = threadIdx.x; b < W * (P / 4); b += kDDThreads) {
+            const int g = b >> lq, j = b & (q - 1);
             const int i0 = g * len + j;
             const cdd w2 = INV ? cconj(tw[2 * j * step]) : tw[2 * j * step];
             const cdd wa = INV ? cconj(tw[j * step]) : tw[j * step];
-            const cdd a0 = x[i0], a1 = cmul(x[i0 + q], w2);
-            const cdd a2 = x[i0 + 2 * q], a3 = cmul(x[i0 + 3 * q], w2);
+            const cdd a0 = x.get(i0), a1 = cmul(x.get(i0 + q), w2);
+            const cdd a2 = x.get(i0 + 2 * q), a3 = cmul(x.get(i0 + 3 * q), w2);
             const cdd b0 = cadd(a0, a1), b1 = csub(a0, a1);
             const cdd b2 = cadd(a2, a3), b3 = csub(a2, a3);
             const cdd t2 = cmul(b2, wa);
             const cdd u3 = cmul(b3, wa);
             const cdd t3 = INV ? cdd{-u3.im, u3.re} : cdd{u3.im, -u3.re};
-            x[i0] = cadd(b0, t2);
-            x[i0 + 2 * q] = csub(b0, t2);
-            x[i0 + q] = cadd(b1, t3);
-            x[i0 + 3 * q] = csub(b1, t3);
+            x.put(i0, cadd(b0, t2));
+            x.put(i0 + 2 * q, csub(b0, t2));
+            x.put(i0 + q, cadd(b1, t3));
+            x.put(i0 + 3 * q, csub(b1, t3));
         }
         __syncthreads();
     }
@@ -183,34 +215,36 @@ __device__ __forceinline__ int bitrev(int t, int logP) {
 // DCT-I along axis ax of the octant (D_j = N_j + 1 points per axis), as the
 // real part of the length-2N DFT of each line's even extension (x[m] for
 // m <= N, x[2N - m] above): sum_m c_m x[m] cos(pi p m / N), c_0 = c_N = 1,
-// else 2.  One line per workgroup; tw: the axis' twiddles of length 2N.
+// else 2.  W lines per workgroup; tw: the axis' twiddles of length 2N.
 __global__ __launch_bounds__(kDDThreads) void k_dd_dct(const dd* __restrict__ in,
                                                      dd* __restrict__ out, DDGeom g, int ax,
-                                                     const cdd* __restrict__ tw) {
-    extern __shared__ cdd x[];
+                                                     long lines, const cdd* __restrict__ tw) {
+    extern __shared__ dd lds[];
     const int D0 = g.N[0] + 1, D1 = g.d > 1 ? g.N[1] + 1 : 1;
-    const int N = g.N[ax], P = 2 * N;
+    const int N = g.N[ax], P = 2 * N, W = dd_lines(P);
+    const DDTile x{lds, lds + W * P};
     int logP = 0;
     while ((1 << logP) < P) ++logP;
-    const long l = blockIdx.x;
-    long base, stride;
-    if (ax == 0) {
-        base = l * D0;  // l = a2 D1 + a1
-        stride = 1;
-    } else if (ax == 1) {
-        base = (l / D0) * (long)D1 * D0 + l % D0;  // l = a2 D0 + a0
-        stride = D0;
-    } else {
-        base = l;  // l = a1 D0 + a0
-        stride = (long)D0 * D1;
-    }
-    for (int t = threadIdx.x; t < P; t += blockDim.x) {
+    const long stride = ax == 0 ? 1 : ax == 1 ? D0 : (long)D0 * D1;
+    auto base = [&](long l) {
+        if (ax == 0) return l * D0;                                       // l = a2 D1 + a1
+        if (ax == 1) return (l / D0) * (long)D1 * D0 + l % D0;            // l = a2 D0 + a0
+        return l;                                                         // l = a1 D0 + a0
+    };
+    const long l0 = (long)blockIdx.x * W;
+    for (int e = threadIdx.x; e < W * P; e += kDDThreads) {
+        // neighbours in memory on neighbouring threads
+        const int w = ax == 0 ? e / P : e % W, t = ax == 0 ? e % P : e / W;
         const int m = t <= N ? t : P - t;
-        x[bitrev(t, logP)] = cdd{in[base + m * stride], dd_of(0.0)};
+        x.put(w * P + bitrev(t, logP),
+              cdd{l0 + w < lines ? in[base(l0 + w) + m * stride] : dd_of(0.0), dd_of(0.0)});
     }
     __syncthreads();
-    dd_fft_lds<false>(x, P, logP, tw);
-    for (int p = threadIdx.x; p <= N; p += blockDim.x) out[base + p * stride] = x[p].re;
+    dd_fft_lds<false>(x, W, P, logP, tw);
+    for (int e = threadIdx.x; e < W * (N + 1); e += kDDThreads) {
+        const int w = ax == 0 ? e / (N + 1) : e % W, p = ax == 0 ? e % (N + 1) : e / W;
+        if (l0 + w < lines) out[base(l0 + w) + p * stride] = x.re[w * P + p];
+    }
 }
 
 // Where a line lives: element t of line l is at base(l) + t * es, with
@@ -228,70 +262,115 @@ struct DDConv {  // octant lookup of T^ along axis-0 lines at (p1, p2)
     int N[3], P[3], D0, D1, d;
 };
 
-// One line: load n_in inputs (the rest zero), transform, store n_out outputs.
+// W lines: load n_in inputs each (the rest zero), transform, store n_out
+// outputs each.  The real modes run along the last axis and take the rows 2l and
+// 2l + 1 of line l as one complex row a + i b (N_0 is even, so rows pair up);
+// their spectra A and B hold the bins 0 .. P/2:
+//   A[k] = (Z[k] + conj Z[P-k]) / 2,  B[k] = (Z[k] - conj Z[P-k]) / 2i.
 template <int MODE>
 __global__ __launch_bounds__(kDDThreads) void k_dd_pass(const void* __restrict__ in,
                                                         void* __restrict__ out, DDLines li,
-                                                        DDLines lo, int P, int logP, int n_in,
-                                                        int n_out, const cdd* __restrict__ tw,
-                                                        DDConv cv) {
-    extern __shared__ cdd x[];
-    const long line = blockIdx.x;
-    const long bi = li.base(line), bo = lo.base(line);
-    for (int t = threadIdx.x; t < P; t += blockDim.x) {
+                                                        DDLines lo, long lines, int P, int logP,
+                                                        int n_in, int n_out,
+                                                        const cdd* __restrict__ tw, DDConv cv) {
+    extern __shared__ dd lds[];
+    const int W = dd_lines(P);
+    const DDTile x{lds, lds + W * P};
+    const long l0 = (long)blockIdx.x * W;
+    for (int e = threadIdx.x; e < W * P; e += kDDThreads) {
         cdd v = cdd{dd_of(0.0), dd_of(0.0)};
-        if (t < n_in) {
-            if constexpr (MODE == DD_FWD_REAL) v.re = ((const dd*)in)[bi + t * li.es];
-            else v = ((const cdd*)in)[bi + t * li.es];
+        int w, t;
+        if constexpr (MODE == DD_FWD_REAL || MODE == DD_INV_REAL) {  // contiguous rows
+            w = e / P;
+            t = e % P;
+        } else {  // neighbouring lines are neighbours in memory
+            w = e % W;
+            t = e / W;
         }
-        x[bitrev(t, logP)] = v;
+        if (l0 + w < lines) {
+            if constexpr (MODE == DD_FWD_REAL) {
+                if (t < n_in) {
+                    v.re = ((const dd*)in)[li.base(2 * (l0 + w)) + t];
+                    v.im = ((const dd*)in)[li.base(2 * (l0 + w) + 1) + t];
+                }
+            } else if constexpr (MODE == DD_INV_REAL) {
+                // Z[k] = A[k] + i B[k], Z[P-k] = conj A[k] + i conj B[k]
+                const int k = t <= P / 2 ? t : P - t;
+                cdd a = ((const cdd*)in)[li.base(2 * (l0 + w)) + k];
+                cdd b = ((const cdd*)in)[li.base(2 * (l0 + w) + 1) + k];
+                if (t > P / 2) {
+                    a = cconj(a);
+                    b = cconj(b);
+                }
+                v = cdd{a.re - b.im, a.im + b.re};
+            } else {
+                if (t < n_in) v = ((const cdd*)in)[li.base(l0 + w) + t * li.es];
+            }
+        }
+        x.put(w * P + bitrev(t, logP), v);
     }
     __syncthreads();
     if constexpr (MODE == DD_CONV) {
-        dd_fft_lds<false>(x, P, logP, tw);
-        // line at (p1, p2) = (line / P2, line % P2) in 3D, p1 = line in 2D
-        int a1, a2 = 0;
-        if (cv.d == 3) {
-            const int p1 = (int)(line / cv.P[2]), p2 = (int)(line % cv.P[2]);
-            a1 = p1 <= cv.N[1] ? p1 : cv.P[1] - p1;
-            a2 = p2 <= cv.N[2] ? p2 : cv.P[2] - p2;
-        } else {
-            const int p1 = (int)line;
-            a1 = p1 <= cv.N[1] ? p1 : cv.P[1] - p1;
-        }
-        const dd* trow = cv.tensor + ((long)a2 * cv.D1 + a1) * cv.D0;
+        dd_fft_lds<false>(x, W, P, logP, tw);
         // x (natural order) times T^, back into bit-reversed order for the
-        // inverse: every product is formed before any is written back (at
-        // most P / blockDim <= 8 per thread)
+        // inverse: every product is formed before any is written back
         // (fixed trip counts keep the array in registers)
-        constexpr int kKeep = kDDMaxP / kDDThreads;  // P / blockDim (blockDim = min(P/4, 256))
-        static_assert(kDDMaxP / kDDThreads <= kKeep, "keep array too small");
+        constexpr int kKeep = kDDMaxP / kDDThreads;  // W P / kDDThreads <= 8
         cdd keep[kKeep];
 #pragma unroll
         for (int r = 0; r < kKeep; ++r) {
-            const int t = threadIdx.x + r * blockDim.x;
-            if (t < P) {
+            const int e = threadIdx.x + r * kDDThreads;
+            const int w = e / P, t = e % P;
+            if (e < W * P && l0 + w < lines) {
+                // line at (p1, p2), p2 <= N_2, in 3D; p1 <= N_1 in 2D
+                const long line = l0 + w;
+                int a1, a2 = 0;
+                if (cv.d == 3) {
+                    const int p1 = (int)(line / (cv.N[2] + 1));
+                    a2 = (int)(line % (cv.N[2] + 1));
+                    a1 = p1 <= cv.N[1] ? p1 : cv.P[1] - p1;
+                } else {
+                    a1 = (int)line;
+                }
                 const int a0 = t <= cv.N[0] ? t : P - t;
-                const dd s = trow[a0];
-                cdd v = x[t];
+                const dd s = cv.tensor[((long)a2 * cv.D1 + a1) * cv.D0 + a0];
+                cdd v = x.get(e);
                 v.re = v.re * s;
                 v.im = v.im * s;
                 keep[r] = v;
+            } else {
+                keep[r] = cdd{dd_of(0.0), dd_of(0.0)};
             }
         }
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kKeep; ++r) {
-            const int t = threadIdx.x + r * blockDim.x;
-            if (t < P) x[bitrev(t, logP)] = keep[r];
+            const int e = threadIdx.x + r * kDDThreads;
+            if (e < W * P) x.put((e / P) * P + bitrev(e % P, logP), keep[r]);
         }
         __syncthreads();
     }
-    if constexpr (MODE == DD_FWD || MODE == DD_FWD_REAL) dd_fft_lds<false>(x, P, logP, tw);
-    else dd_fft_lds<true>(x, P, logP, tw);
-    for (int t = threadIdx.x; t < n_out; t += blockDim.x) {
-        if constexpr (MODE == DD_INV_REAL) ((dd*)out)[bo + t * lo.es] = x[t].re;
-        else ((cdd*)out)[bo + t * lo.es] = x[t];
+    if constexpr (MODE == DD_FWD || MODE == DD_FWD_REAL) dd_fft_lds<false>(x, W, P, logP, tw);
+    else dd_fft_lds<true>(x, W, P, logP, tw);
+    for (int e = threadIdx.x; e < W * n_out; e += kDDThreads) {
+        if constexpr (MODE == DD_FWD_REAL || MODE == DD_INV_REAL) {
+            const int w = e / n_out, t = e % n_out;
+            if (l0 + w >= lines) continue;
+            const long ba = lo.base(2 * (l0 + w)) + t, bb = lo.base(2 * (l0 + w) + 1) + t;
+            const cdd z = x.get(w * P + t);
+            if constexpr (MODE == DD_FWD_REAL) {
+                const cdd c = cconj(x.get(w * P + (t == 0 ? 0 : P - t)));
+                const cdd a = cadd(z, c), b = csub(z, c);
+                ((cdd*)out)[ba] = cdd{a.re * 0.5, a.im * 0.5};
+                ((cdd*)out)[bb] = cdd{b.im * 0.5, -(b.re * 0.5)};
+            } else {
+                ((dd*)out)[ba] = z.re;
+                ((dd*)out)[bb] = z.im;
+            }
+        } else {
+            const int w = e % W, t = e / W;
+            if (l0 + w < lines) ((cdd*)out)[lo.base(l0 + w) + t * lo.es] = x.get(w * P + t);
+        }
     }
 }
 
@@ -343,10 +422,10 @@ hipError_t build_tensor_dd(const fsa_plan_s* pl, hipStream_t st) {
         for (int ax = 0; ax < pl->d; ++ax) {
             const int P = 2 * g.N[ax];
             const long lines = n / (g.N[ax] + 1);
-            const int threads = dd_threads(P);
-            hipLaunchKernelGGL(k_dd_dct, dim3((unsigned)lines), dim3(threads),
-                               sizeof(cdd) * (size_t)P, st, (const dd*)src, dst, g, ax,
-                               dd_tw(pl, ax));
+            const int W = dd_lines(P);
+            hipLaunchKernelGGL(k_dd_dct, dim3((unsigned)((lines + W - 1) / W)), dim3(kDDThreads),
+                               sizeof(cdd) * (size_t)(W * P), st, (const dd*)src, dst, g, ax,
+                               lines, dd_tw(pl, ax));
             dd* t = src;
             src = dst;
             dst = t;
@@ -360,8 +439,8 @@ hipError_t build_tensor_dd(const fsa_plan_s* pl, hipStream_t st) {
     return e;
 }
 
-// Step k of a double-double evaluation (2d - 1 launches).  X is the full
-// padded complex array, C order (P_0, ..., P_{d-1}).
+// Step k of a double-double evaluation (2d - 1 launches).  X holds the padded
+// spectrum's bins 0 .. N_last of the last axis, C order (P_0, ..., N_last + 1).
 hipError_t launch_dd_step(const fsa_plan_s* pl, int k, const void* rho, void* phi, void* ws,
                           hipStream_t st) {
     const int d = pl->d;
@@ -382,6 +461,7 @@ hipError_t launch_dd_step(const fsa_plan_s* pl, int k, const void* rho, void* ph
         cv.N[j] = j < d ? (int)N[j] : 0;
         cv.P[j] = j < d ? (int)P[j] : 1;
     }
+    const long H = N[d - 1] + 1;  // kept bins of the last axis
     cv.D0 = (int)N[0] + 1;
     cv.D1 = (int)N[1] + 1;
     // pass kinds in order: fwd last (real in), [fwd axis 1], conv axis 0,
@@ -404,83 +484,84 @@ hipError_t launch_dd_step(const fsa_plan_s* pl, int k, const void* rho, void* ph
     int n_in = 0, n_out = 0;
     if (d == 3) {
         switch (mode) {
-        case DD_FWD_REAL:  // rows (i0 < N0, i1 < N1) of rho -> X[i0][i1][p2]
-            lines = N[0] * N[1];
+        case DD_FWD_REAL:  // pairs of rows (i0 < N0, i1 < N1) of rho -> X[i0][i1][p2]
+            lines = N[0] * N[1] / 2;
             li = DDLines{N[1] * N[2], N[2], 1, (int)N[1]};
-            lo = DDLines{P[1] * P[2], P[2], 1, (int)N[1]};
+            lo = DDLines{P[1] * H, H, 1, (int)N[1]};
             n_in = (int)N[2];
-            n_out = (int)P[2];
+            n_out = (int)H;
             break;
         case DD_FWD:  // axis 1 at (i0 < N0, p2): X[i0][t][p2]
-            lines = N[0] * P[2];
-            li = lo = DDLines{P[1] * P[2], 1, P[2], (int)P[2]};
+            lines = N[0] * H;
+            li = lo = DDLines{P[1] * H, 1, H, (int)H};
             n_in = (int)N[1];
             n_out = (int)P[1];
             break;
         case DD_CONV:  // axis 0 at (p1, p2): X[t][p1][p2]
-            lines = P[1] * P[2];
-            li = lo = DDLines{P[2], 1, P[1] * P[2], (int)P[2]};
+            lines = P[1] * H;
+            li = lo = DDLines{H, 1, P[1] * H, (int)H};
             n_in = n_out = (int)N[0];
             break;
         case DD_INV:
-            lines = N[0] * P[2];
-            li = lo = DDLines{P[1] * P[2], 1, P[2], (int)P[2]};
+            lines = N[0] * H;
+            li = lo = DDLines{P[1] * H, 1, H, (int)H};
             n_in = (int)P[1];
             n_out = (int)N[1];
             break;
-        default:  // DD_INV_REAL: X[i0][i1][t] -> phi rows
-            lines = N[0] * N[1];
-            li = DDLines{P[1] * P[2], P[2], 1, (int)N[1]};
+        default:  // DD_INV_REAL: X[i0][i1][t] -> pairs of phi rows
+            lines = N[0] * N[1] / 2;
+            li = DDLines{P[1] * H, H, 1, (int)N[1]};
             lo = DDLines{N[1] * N[2], N[2], 1, (int)N[1]};
-            n_in = (int)P[2];
+            n_in = (int)H;
             n_out = (int)N[2];
             break;
         }
     } else {
         switch (mode) {
-        case DD_FWD_REAL:  // rows i0 < N0 -> X[i0][p1]
-            lines = N[0];
+        case DD_FWD_REAL:  // pairs of rows i0 < N0 -> X[i0][p1]
+            lines = N[0] / 2;
             li = DDLines{N[1], 0, 1, 1};
-            lo = DDLines{P[1], 0, 1, 1};
+            lo = DDLines{H, 0, 1, 1};
             n_in = (int)N[1];
-            n_out = (int)P[1];
+            n_out = (int)H;
             break;
         case DD_CONV:  // axis 0 at p1: X[t][p1]
-            lines = P[1];
-            li = lo = DDLines{1, 0, P[1], 1};
+            lines = H;
+            li = lo = DDLines{1, 0, H, 1};
             n_in = n_out = (int)N[0];
             break;
         default:
-            lines = N[0];
-            li = DDLines{P[1], 0, 1, 1};
+            lines = N[0] / 2;
+            li = DDLines{H, 0, 1, 1};
             lo = DDLines{N[1], 0, 1, 1};
-            n_in = (int)P[1];
+            n_in = (int)H;
             n_out = (int)N[1];
             break;
         }
     }
     if (Pa > kDDMaxP || lines <= 0 || lines > 0x7fffffffL) return hipErrorInvalidValue;
-    const int threads = dd_threads(Pa);
-    const size_t lds = sizeof(cdd) * (size_t)Pa;
+    const int W = dd_lines(Pa);
+    const dim3 grid((unsigned)((lines + W - 1) / W)), block(kDDThreads);
+    const size_t lds = sizeof(cdd) * (size_t)(W * Pa);
     const cdd* tw = dd_tw(pl, ax);
     const void* src = mode == DD_FWD_REAL ? rho : (const void*)X;
     void* dst = mode == DD_INV_REAL ? phi : (void*)X;
     switch (mode) {
     case DD_FWD_REAL:
-        return launch_kernel(k_dd_pass<DD_FWD_REAL>, dim3((unsigned)lines), dim3(threads), lds, st,
-                             src, dst, li, lo, Pa, lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_FWD_REAL>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
+                             lg, n_in, n_out, tw, cv);
     case DD_FWD:
-        return launch_kernel(k_dd_pass<DD_FWD>, dim3((unsigned)lines), dim3(threads), lds, st,
-                             src, dst, li, lo, Pa, lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_FWD>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
+                             lg, n_in, n_out, tw, cv);
     case DD_CONV:
-        return launch_kernel(k_dd_pass<DD_CONV>, dim3((unsigned)lines), dim3(threads), lds, st,
-                             src, dst, li, lo, Pa, lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_CONV>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
+                             lg, n_in, n_out, tw, cv);
     case DD_INV:
-        return launch_kernel(k_dd_pass<DD_INV>, dim3((unsigned)lines), dim3(threads), lds, st,
-                             src, dst, li, lo, Pa, lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_INV>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
+                             lg, n_in, n_out, tw, cv);
     default:
-        return launch_kernel(k_dd_pass<DD_INV_REAL>, dim3((unsigned)lines), dim3(threads), lds, st,
-                             src, dst, li, lo, Pa, lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_INV_REAL>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
+                             lg, n_in, n_out, tw, cv);
     }
 }
 
