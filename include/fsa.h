@@ -169,7 +169,8 @@ fsa_status fsa_plan_query(fsa_plan plan, double* eps_used, double* h, size_t* te
 fsa_status fsa_build_tensor(fsa_plan plan, void* stream);
 
 /* One evaluation (Execution in the paper's terms): phi = crop(IDFT(T^ .
- * DFT(pad(rho)))) through 3 (2D) or 5 (3D) kernels enqueued on `stream`;
+ * DFT(pad(rho)))) through 3 (2D) or 5 (3D) kernels enqueued on `stream` (3 on
+ * small 3D grids, N_0 N_1 <= 2048, whose three middle passes run as one);
  * returns without host synchronisation.
  *   rho        device input, plan precision, shape N (read only).
  *   phi        device output, plan precision, shape N; may equal rho.
@@ -199,13 +200,15 @@ fsa_status fsa_apply(fsa_plan plan, const void* rho, void* phi, void* workspace,
  * -- race and give wrong results; order them on one stream. */
 fsa_status fsa_apply_noalloc(fsa_plan plan, const void* rho, void* phi, void* stream);
 
-/* Number of kernel launches of one evaluation with the plan's current
+/* Number of kernel launches of one evaluation with every pass in a launch of
+ * its own, as fsa_apply_events runs it, under the plan's current
  * schedule (3 in 2D; 2 + 3 x slabs in 3D, see fsa_tune_set_slabs) and, if
  * `passes` is not NULL, the fsa_pass of each launch in order (cap entries
  * available). */
 fsa_status fsa_plan_launches(fsa_plan plan, int* n, int* passes, int cap);
 
-/* Profiling variant of fsa_apply: the same kernels on the same stream, with
+/* Profiling variant of fsa_apply: every pass in a launch of its own (also where
+ * fsa_apply runs several as one; the results are bitwise the same), with
  * hipEventRecord(events[2i], stream) right before launch i (of n, from
  * fsa_plan_launches) and hipEventRecord(events[2i + 1], stream) right after
  * it, so that hipEventElapsedTime(events[2i], events[2i + 1]) times launch i.

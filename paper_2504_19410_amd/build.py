@@ -35,6 +35,8 @@ SOURCES = [
     "fsa_launch_f64_v2.hip",
     "fsa_launch_f64_v3.hip",
     "fsa_launch_f64_v4.hip",
+    "fsa_plane_f32.hip",
+    "fsa_plane_f64.hip",
 ]
 
 CXXFLAGS = [

@@ -315,6 +315,8 @@ static hipError_t launch_pass_t(const fsa_plan_s* pl, int k, int lo, int n, cons
         case 2:
             return Launch<R>::conv(2 * N0, w2, tensor, n * 2 * N1, 2 * N1, N1, lo, tw_p0, c, st);
         case 3: return Launch<R>::inv_t(2 * N1, w2, w1, N0, H, lo, n, tw_p1, c, st);
+        case kPlaneStep:
+            return PlaneV<R>::launch(2 * N1, 2 * N0, JobPlane{w1, tensor, H}, tw_p1, tw_p0, st);
         case 4:
             return Launch<R>::c2r(N2, w1, (R*)phi, N0, N1, add, alpha, tw_m, tw_pl, c, st);
         }
@@ -337,7 +339,7 @@ static hipError_t launch_pass_t(const fsa_plan_s* pl, int k, int lo, int n, cons
 hipError_t launch_step(const fsa_plan_s* pl, const Step& s, const void* rho, void* phi, void* ws,
                        Choice c, hipStream_t st) {
     if (pl->prec == FSA_DD) return launch_dd_step(pl, s.k, rho, phi, ws, st);
-    if (s.k >= kSpectralStep) {  // derivative of a dipole-dipole plan
+    if (s.k >= kSpectralStep && s.k != kPlaneStep) {  // derivative of a dipole-dipole plan
         char* w1 = (char*)ws;
         char* w2 = w1 + ((pl->ws1_elems * pl->csize + 255) & ~size_t(255));
         return spectral_step(pl, s.k - kSpectralStep, rho, w1, w2, st);
@@ -371,6 +373,29 @@ int schedule(const fsa_plan_s* pl, int slabs, Step* out) {
     return m;
 }
 
+bool plane_family(const fsa_plan_s* pl, int k, int var) {
+    const bool f32 = pl->prec == FSA_F32;
+    const int P0 = (int)(2 * pl->N[0]);
+    return k == 2 ? conv_family(f32, P0, var) == plane_conv_alt(f32, P0) : var != 1;
+}
+
+int schedule_plane(const fsa_plan_s* pl, Step* out) {
+    if (pl->d != 3 || pl->prec == FSA_DD || tune::get_slabs(pl) != 1) return 0;
+    const int P0 = (int)(2 * pl->N[0]), P1 = (int)(2 * pl->N[1]), H = (int)pl->H;
+    const bool f32 = pl->prec == FSA_F32;
+    if (!(f32 ? PlaneV<float>::fits(P1, P0) : PlaneV<double>::fits(P1, P0))) return 0;
+    // only where it computes what the launches chosen for the passes compute:
+    // the default radix family in passes B and D, plane_conv_alt's in pass C
+    for (int k = 1; k <= 3; ++k)
+        if (!plane_family(pl, k, step_choice(pl, Step{k, 0, H}).var)) return 0;
+    int m = 0;
+    for (int i = 0; i < pl->n_spectral; ++i) out[m++] = Step{kSpectralStep + i, 0, 0};
+    out[m++] = Step{0, 0, H};
+    out[m++] = Step{kPlaneStep, 0, H};
+    out[m++] = Step{4, 0, H};
+    return m;
+}
+
 long step_lines(const fsa_plan_s* pl, const Step& s) {
     const long N0 = pl->N[0], N1 = pl->N[1];
     if (pl->d == 3) {
@@ -399,15 +424,17 @@ Choice step_choice(const fsa_plan_s* pl, const Step& s) {
 // launch i and ev[2i + 1] right after it (a null pair: launch i untimed).
 static hipError_t apply_impl(const fsa_plan_s* pl, const void* rho, void* phi, void* ws,
                              hipStream_t st, hipEvent_t const* ev) {
-    static const char* const kPassRange[6] = {"fsa pass A r2c", "fsa pass B fwd_t",
+    static const char* const kPassRange[7] = {"fsa pass A r2c", "fsa pass B fwd_t",
                                               "fsa pass C conv", "fsa pass D inv_t",
-                                              "fsa pass E c2r", "fsa spectral"};
+                                              "fsa pass E c2r", "fsa spectral",
+                                              "fsa passes B, C, D"};
     Range range("fsa_apply");
     Step steps[kMaxSteps];
-    const int ns = schedule(pl, tune::get_slabs(pl), steps);
+    int ns = ev ? 0 : schedule_plane(pl, steps);
+    if (ns == 0) ns = schedule(pl, tune::get_slabs(pl), steps);
     hipError_t e = hipSuccess;
     for (int i = 0; i < ns && e == hipSuccess; ++i) {
-        int kind = steps[i].k >= kSpectralStep ? 5 : steps[i].k;
+        int kind = steps[i].k == kPlaneStep ? 6 : steps[i].k >= kSpectralStep ? 5 : steps[i].k;
         if (kind < 5 && pl->prec != FSA_DD && pl->d == 2) kind = kind == 0 ? 0 : kind == 1 ? 2 : 4;
         Range pass_range(kPassRange[kind]);
         const bool timed = ev && ev[2 * i];

@@ -51,11 +51,20 @@ template <typename R>
 FSA_HD cpx<R> operator+(cpx<R> a, cpx<R> b) { return mk(a.x + b.x, a.y + b.y); }
 template <typename R>
 FSA_HD cpx<R> operator-(cpx<R> a, cpx<R> b) { return mk(a.x - b.x, a.y - b.y); }
+// Which product of a complex multiplication is fused into its sum is written
+// out: left to contraction the compiler decides it by the surrounding code, and
+// the same transform would round differently from kernel to kernel.
+FSA_HD float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+FSA_HD double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <typename R>
-FSA_HD cpx<R> cmul(cpx<R> a, cpx<R> b) { return mk(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
+FSA_HD cpx<R> cmul(cpx<R> a, cpx<R> b) {
+    return mk(fmadd(a.x, b.x, -(a.y * b.y)), fmadd(a.x, b.y, a.y * b.x));
+}
 // a * conj(b)
 template <typename R>
-FSA_HD cpx<R> cmulc(cpx<R> a, cpx<R> b) { return mk(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y); }
+FSA_HD cpx<R> cmulc(cpx<R> a, cpx<R> b) {
+    return mk(fmadd(a.x, b.x, a.y * b.y), fmadd(a.y, b.x, -(a.x * b.y)));
+}
 template <typename R>
 FSA_HD cpx<R> conj(cpx<R> a) { return mk(a.x, -a.y); }
 template <typename R>
@@ -80,12 +89,12 @@ template <bool INV, typename R>
 FSA_HD void dft3(cpx<R>* a) {
     const R c = R(-0.5), s = R(0.86602540378443864676372317075294);  // sin(2 pi / 3)
     const cpx<R> t = a[1] + a[2];
-    const cpx<R> m = a[0] + scale(t, c);
-    // (a1 - a2) * (-/+ i sin(2pi/3))
-    const cpx<R> d = scale(rot90<INV>(a[1] - a[2]), s);
+    const cpx<R> m = mk(fmadd(t.x, c, a[0].x), fmadd(t.y, c, a[0].y));
+    // (a1 - a2) * (-/+ i), times sin(2pi/3) below
+    const cpx<R> d = rot90<INV>(a[1] - a[2]);
     a[0] = a[0] + t;
-    a[1] = m + d;
-    a[2] = m - d;
+    a[1] = mk(fmadd(d.x, s, m.x), fmadd(d.y, s, m.y));
+    a[2] = mk(fmadd(d.x, -s, m.x), fmadd(d.y, -s, m.y));
 }
 
 template <bool INV, typename R>
@@ -166,7 +175,7 @@ FSA_HD cpx<R> w12(cpx<R> a) {
     else if constexpr (k == 6) return mk(-a.x, -a.y);
     else {
         const R s = INV ? sn : -sn;  // w = cs + i s
-        return mk(a.x * cs - a.y * s, a.x * s + a.y * cs);
+        return mk(fmadd(a.x, cs, -(a.y * s)), fmadd(a.x, s, a.y * cs));
     }
 }
 
@@ -458,10 +467,14 @@ constexpr bool fft_length_supported(long P) {
 // that, and the work-item, pencil and tensor-row arithmetic derived from it
 // runs once per wave on the scalar unit instead of on every lane.
 template <int T>
-__device__ __forceinline__ int team_index() {
-    const int t = (int)threadIdx.x / T;
+__device__ __forceinline__ int team_of(int thread) {
+    const int t = thread / T;
     if constexpr (T % 64 == 0) return __builtin_amdgcn_readfirstlane(t);
     else return t;
+}
+template <int T>
+__device__ __forceinline__ int team_index() {
+    return team_of<T>((int)threadIdx.x);
 }
 
 #endif
@@ -831,6 +844,27 @@ struct Fft {
                 if (idx < n_out) f(idx, v[b * RAD + q]);
             }
         }
+    }
+
+    // The last-stage outputs of the lower half (index < P/2) as register slots, in
+    // a fixed order: g(value) of each, and f(index, exists) of each.
+    template <class G>
+    FSA_HD static void store_last_slots(const C (&v)[V], int, G&& g) {
+#pragma unroll
+        for (int b = 0; b < last_nbt(); ++b)
+#pragma unroll
+            for (int q = 0; q < last_radix() / 2; ++q) g(v[b * last_radix() + q]);
+    }
+    template <class G>
+    FSA_HD static void last_slots(int tid, G&& f) {
+        static_assert(radix(S - 1) % 2 == 0, "the lower half = whole last-stage outputs");
+#pragma unroll
+        for (int b = 0; b < last_nbt(); ++b)
+#pragma unroll
+            for (int q = 0; q < last_radix() / 2; ++q) {
+                const int j = tid + b * T;
+                f(j + q * last_stride(), (nb(S - 1) % T) == 0 || j < nb(S - 1));
+            }
     }
 
     // apply g(index, value&) to every last-stage output held by this thread

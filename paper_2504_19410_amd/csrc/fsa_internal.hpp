@@ -134,6 +134,15 @@ struct LaunchV {
     static int max_occ(Pass pass, int len);
 };
 
+// Passes B, C and D of small planes in one launch (fsa_plane_<prec>.hip).
+template <typename R>
+struct PlaneV {
+    static hipError_t launch(int P1, int P0, const JobPlane& jb, const void* tw1, const void* tw0,
+                             hipStream_t st);
+    // Whether a plane of these padded lengths fits a workgroup.
+    static bool fits(int P1, int P0);
+};
+
 // Dispatch on the run-time choice.
 template <typename R>
 struct Launch {
@@ -233,10 +242,17 @@ constexpr int kMaxSlabs = 16;
 // a dipole-dipole plan runs its n_spectral (at most kSpectralSteps)
 // derivative launches first, as steps k = kSpectralStep + i
 constexpr int kSpectralStep = 5, kSpectralSteps = 5;
+// passes B, C and D in one launch (fsa_plane.hpp)
+constexpr int kPlaneStep = kSpectralStep + kSpectralSteps;
 constexpr int kMaxSteps = 2 + 3 * kMaxSlabs + kSpectralSteps;
 // Launch order of one evaluation with `slabs` slabs of bins (clamped to
 // [1, min(H, kMaxSlabs)]; 2D plans always have 3 launches).
 int schedule(const fsa_plan_s* pl, int slabs, Step* out);
+// The same with passes B, C and D in one launch, where fsa_apply runs them so
+// (0: it does not; `schedule` then gives the launches).
+int schedule_plane(const fsa_plan_s* pl, Step* out);
+// Whether variant var of pass k (1 .. 3) computes what that launch computes.
+bool plane_family(const fsa_plan_s* pl, int k, int var);
 hipError_t launch_step(const fsa_plan_s* pl, const Step& s, const void* rho, void* phi, void* ws,
                        Choice c, hipStream_t st);
 Choice step_choice(const fsa_plan_s* pl, const Step& s);

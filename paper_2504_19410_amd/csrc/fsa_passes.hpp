@@ -613,18 +613,9 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
 // and items are ordered so that the mirror pencils p1 and P1 - p1, which read
 // the same tensor row, follow each other.
 // ---------------------------------------------------------------------------
-// Radix family of pass C: at length 256 in FP32 variant 0 is 16 x 16 (one
-// exchange through the LDS) and variant 1 is 8 x 4 x 8 (two); 19.4 against 23.5
-// us at 128^3, 32.4 against 39.4 at 128 x 128 x 256, equal at 128 x 1024 x 64.
-// In FP64 16 operands per thread cost what the exchange saves.
-template <typename R, int P>
-constexpr int conv_alt(int var) {
-    return sizeof(R) == 4 && P == 256 ? 1 - var_alt(var) : var_alt(var);
-}
-
 template <typename R, int P, int VAR = 0>
 struct Conv {
-    static constexpr int ALT = conv_alt<R, P>(VAR);
+    static constexpr int ALT = conv_family(sizeof(R) == 4, P, VAR);
     using Ff = Fft<R, P, false, ALT, var_xch(VAR)>;
     using Fi = Fft<R, P, true, ALT, var_xch(VAR)>;
     using C = cpx<R>;

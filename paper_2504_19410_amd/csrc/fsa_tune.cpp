@@ -608,6 +608,8 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
             }
         return r;
     };
+    std::vector<fsa::Choice> cands_of[5];
+    std::vector<double> us_of[5];
     // one evaluation with the current choices fills every buffer with data
     if (e == hipSuccess) e = run_all(1);
     for (int k = 0; k < np && e == hipSuccess; ++k) {
@@ -647,6 +649,8 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
             for (size_t c = 1; c < cands.size(); ++c)
                 if (us[c] < us[b]) b = c;
             fsa::tune::set(pl->prec, pass, len, fsa::step_lines(pl, whole(k)), cands[b], us[b]);
+            cands_of[k] = cands;
+            us_of[k] = us;
         }
     }
     // schedule: slabs of bins for the middle passes (3D)
@@ -670,6 +674,65 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
             for (size_t c = 1; c < counts.size(); ++c)
                 if (us[c] < us[b]) b = c;
             fsa::tune::set_slabs(pl, counts[b], us[b] / kBack);
+            const double apart = us[b] / kBack;
+            // passes B, C and D of a small plane in one launch: it computes what
+            // one radix family of each pass computes, so the fastest choices of
+            // those families stand in the table while it is timed, and stay if it
+            // is the faster schedule
+            fsa::Choice best[5], match[5];
+            double best_us[5], match_us[5];
+            bool have = true;
+            for (int k = 1; k <= 3; ++k) {
+                size_t w = 0, f = cands_of[k].size();
+                for (size_t c = 0; c < cands_of[k].size(); ++c) {
+                    if (us_of[k][c] < us_of[k][w]) w = c;
+                    if (fsa::plane_family(pl, k, cands_of[k][c].var) &&
+                        (f == cands_of[k].size() || us_of[k][c] < us_of[k][f]))
+                        f = c;
+                }
+                have = have && f < cands_of[k].size();
+                if (!have) break;
+                best[k] = cands_of[k][w];
+                best_us[k] = us_of[k][w];
+                match[k] = cands_of[k][f];
+                match_us[k] = us_of[k][f];
+            }
+            auto set_passes = [&](const fsa::Choice* ch, const double* t) {
+                for (int k = 1; k <= 3; ++k) {
+                    fsa::Pass pass;
+                    int len;
+                    fsa::pass_of(pl, k, &pass, &len);
+                    fsa::tune::set(pl->prec, pass, len, fsa::step_lines(pl, whole(k)), ch[k], t[k]);
+                }
+            };
+            fsa::Step steps[fsa::kMaxSteps];
+            int ns = 0;
+            if (have) {
+                set_passes(match, match_us);
+                fsa::tune::set_slabs(pl, 1, apart);
+                ns = fsa::schedule_plane(pl, steps);
+            }
+            if (ns > 0) {
+                std::vector<double> one;
+                e = time_rounds(1, nothing,
+                                [&](int) {
+                                    hipError_t r = hipSuccess;
+                                    for (int i = 0; i < kBack && r == hipSuccess; ++i)
+                                        for (int j = 0; j < ns && r == hipSuccess; ++j)
+                                            r = fsa::launch_step(pl, steps[j], rho, phi, workspace,
+                                                                 fsa::step_choice(pl, steps[j]), st);
+                                    return r;
+                                },
+                                nothing, one);
+                if (e == hipSuccess && one[0] / kBack < apart)
+                    fsa::tune::set_slabs(pl, 1, one[0] / kBack);
+                else
+                    ns = 0;
+            }
+            if (have && ns == 0) {
+                set_passes(best, best_us);
+                fsa::tune::set_slabs(pl, counts[b], apart);
+            }
         }
     }
     // leave the caller's buffers holding a valid evaluation
