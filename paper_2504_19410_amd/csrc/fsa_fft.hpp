@@ -736,9 +736,10 @@ struct Fft {
         return true;
     }
 
-    // write the outputs of stage s to the scratch
-    template <int s>
-    FSA_HD static void store(const C (&v)[V], C* scr, int tid) {
+    // write the outputs of stage s to the scratch (a pointer, or anything indexed
+    // like one)
+    template <int s, class Scr>
+    FSA_HD static void store(const C (&v)[V], Scr scr, int tid) {
         constexpr int RAD = radix(s), NS = ns(s), NB = nb(s), NBT = nbt(s);
 #pragma unroll
         for (int b = 0; b < NBT; ++b) {
@@ -752,8 +753,8 @@ struct Fft {
     }
 
     // read the inputs of stage s from the scratch
-    template <int s>
-    FSA_HD static void load(C (&v)[V], const C* scr, int tid) {
+    template <int s, class Scr>
+    FSA_HD static void load(C (&v)[V], Scr scr, int tid) {
         constexpr int RAD = radix(s), NB = nb(s), NBT = nbt(s);
 #pragma unroll
         for (int b = 0; b < NBT; ++b) {
@@ -1004,6 +1005,27 @@ struct Fft {
                                                  const C* __restrict__ st) {
         compute_st<0, ZH>(v, tid, st);
         run_g_from<1>(v, scr, tid, st);
+    }
+
+    // run_g through a scratch of any kind (store, load), with its synchronisation:
+    // teams whose threads are not neighbours
+    template <int s, class Scr, class Sync>
+    static __device__ __forceinline__ void run_x_from(C (&v)[V], Scr scr, int tid,
+                                                      const C* __restrict__ st, Sync&& sync) {
+        if constexpr (s < S) {
+            store<s - 1>(v, scr, tid);
+            sync();
+            load<s>(v, scr, tid);
+            sync();
+            compute_st<s>(v, tid, st);
+            run_x_from<s + 1>(v, scr, tid, st, sync);
+        }
+    }
+    template <class Scr, class Sync>
+    static __device__ __forceinline__ void run_x(C (&v)[V], Scr scr, int tid,
+                                                 const C* __restrict__ st, Sync&& sync) {
+        compute_st<0>(v, tid, st);
+        run_x_from<1>(v, scr, tid, st, sync);
     }
 
     // Whether this thread's twiddles fit a register budget of ~56 VGPRs; the
