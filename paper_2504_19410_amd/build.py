@@ -43,6 +43,11 @@ CXXFLAGS = [
     "-x", "hip", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # and from pairing LDS accesses (ds_read2_b64 and ds_write2_b64): a paired FP32
+    # exchange meets the banks its two halves miss one at a time, and its
+    # register quads cost registers (pass C at 192^3 65.3 -> 60.4 us, at 384^3
+    # 611 -> 568; FP64 accesses, 16 bytes wide, are never paired)
+    "-Xclang", "-target-feature", "-Xclang", "-load-store-opt",
     "-Wall", "-Wno-unused-function",
 ]
 

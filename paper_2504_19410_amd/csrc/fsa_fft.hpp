@@ -495,6 +495,14 @@ struct Fft {
     static constexpr int SCR = P_ + (P_ >> 3) + 1;
 
     FSA_HD static constexpr int pad(int i) { return i + (i >> 3); }
+    // pad(base + d), BASE + OFFSET apart where no sum of their residues modulo 8
+    // reaches 8 (SPLIT): the slots of one butterfly are then constants from its
+    // first one, which go into the LDS instructions, instead of three integer
+    // instructions each.
+    template <bool SPLIT>
+    FSA_HD static constexpr int pad_at(int base, int d) {
+        return SPLIT ? pad(base) + pad(d) : pad(base + d);
+    }
 
     // radix of execution stage s (inverse runs the forward radices reversed)
     static constexpr int radix(int s) { return INV ? plan.r[S - 1 - s] : plan.r[s]; }
@@ -736,6 +744,14 @@ struct Fft {
         return true;
     }
 
+    // whether the slots of stage s split (pad_at): outputs base + q NS with
+    // base = (j / NS) NS RAD + j % NS, inputs j + q NB
+    static constexpr bool store_splits(int s) {
+        const int n = ns(s), m = n * radix(s);
+        return n % 8 == 0 || (8 % n == 0 && (m % 8 == 0 || 8 % m == 0));
+    }
+    static constexpr bool load_splits(int s) { return nb(s) % 8 == 0; }
+
     // write the outputs of stage s to the scratch (a pointer, or anything indexed
     // like one)
     template <int s, class Scr>
@@ -748,7 +764,7 @@ struct Fft {
             const int k = j % NS;
             const int base = (j / NS) * NS * RAD + k;
 #pragma unroll
-            for (int q = 0; q < RAD; ++q) scr[pad(base + q * NS)] = v[b * RAD + q];
+            for (int q = 0; q < RAD; ++q) scr[pad_at<store_splits(s)>(base, q * NS)] = v[b * RAD + q];
         }
     }
 
@@ -761,7 +777,7 @@ struct Fft {
             const int j = tid + b * T;
             if ((NB % T) != 0 && j >= NB) continue;
 #pragma unroll
-            for (int q = 0; q < RAD; ++q) v[b * RAD + q] = scr[pad(j + q * NB)];
+            for (int q = 0; q < RAD; ++q) v[b * RAD + q] = scr[pad_at<load_splits(s)>(j, q * NB)];
         }
     }
 
@@ -779,7 +795,7 @@ struct Fft {
             const int base = (j / NS) * NS * RAD + k;
 #pragma unroll
             for (int q = 0; q < RAD; ++q)
-                scr[pad(base + q * NS)] = PART ? v[b * RAD + q].y : v[b * RAD + q].x;
+                scr[pad_at<store_splits(s)>(base, q * NS)] = PART ? v[b * RAD + q].y : v[b * RAD + q].x;
         }
     }
     template <int s, int PART>
@@ -791,8 +807,8 @@ struct Fft {
             if ((NB % T) != 0 && j >= NB) continue;
 #pragma unroll
             for (int q = 0; q < RAD; ++q) {
-                if constexpr (PART) v[b * RAD + q].y = scr[pad(j + q * NB)];
-                else v[b * RAD + q].x = scr[pad(j + q * NB)];
+                if constexpr (PART) v[b * RAD + q].y = scr[pad_at<load_splits(s)>(j, q * NB)];
+                else v[b * RAD + q].x = scr[pad_at<load_splits(s)>(j, q * NB)];
             }
         }
     }
