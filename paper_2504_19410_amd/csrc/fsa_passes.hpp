@@ -607,11 +607,11 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
 //   pencil q = p2 * P1 + p1 (3D) or q = p1 (2D: P1 = 1, N1 = 0),
 //   data[q * N0 + i0];  tensor[((p2 (N1+1) + |p1|) (N0+1)) + |p0|]
 //
-// Persistent: the grid fills the GPU once; every team walks a contiguous
-// chunk of work items.  Its twiddles are loaded into registers once, the next
-// pencil's non-zero half is prefetched while the current one is transformed,
-// and items are ordered so that the mirror pencils p1 and P1 - p1, which read
-// the same tensor row, follow each other.
+// Persistent: the grid fills the GPU once; every workgroup walks a contiguous
+// chunk of work items, its teams side by side (kWalkEven).  A team's twiddles
+// are loaded into registers once, the next pencil's non-zero half is prefetched
+// while the current one is transformed, and items are ordered so that the mirror
+// pencils p1 and P1 - p1, which read the same tensor row, go to neighbours.
 // ---------------------------------------------------------------------------
 template <typename R, int P, int VAR = 0>
 struct Conv {
@@ -686,9 +686,9 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
     if constexpr (REG && !K::SHARED_TW) Fi::load_tw_st(wi, tid, sti);
 
     const int total = src.total;
-    const int slots = gridDim.x * K::TPW;
-    const int chunk = (total + slots - 1) / slots;
-    const int first = (blockIdx.x * K::TPW + team) * chunk;
+    const Walk wk = Walk::make<kWalkEven>(cdiv(total, K::TPW), gridDim.x, blockIdx.x);
+    const int chunk = wk.last - wk.first;
+    const int first = wk.first * K::TPW + team;
 
     C pf[(K::MFMA0 || !K::PREFETCH) ? 1 : K::NPF];
     // variant 4: this lane's B operands (butterfly group g, K step ks at
@@ -730,7 +730,7 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
     if constexpr (K::PREFETCH) prefetch(first);
     for (int it = 0; it < chunk; ++it) {
         const int tid = fresh_lane_conv<R, P>() ? opaque(tid0) : tid0;  // per item: fresh_lane
-        const int item = first + it;
+        const int item = first + it * K::TPW;
         const bool active = item < total;
         int loc;
         const JobConv jb = src.get(active ? item : 0, loc, cur_it);
@@ -762,7 +762,7 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
                 }
         }
         if constexpr (K::PREFETCH) {
-            if (it + 1 < chunk) prefetch(item + 1);
+            if (it + 1 < chunk) prefetch(item + K::TPW);
         }
         const int qp = conv_item_to_pencil(loc, jb.P1, jb.N1) + jb.p2_lo * jb.P1;
         const int p2 = qp / jb.P1, p1 = qp - p2 * jb.P1;

@@ -30,7 +30,16 @@ namespace fsa {
 // XCD (g and g + 8) that run side by side, each stepping two items at a time
 // through the pair chunk of the two; the pairs take contiguous chunks like
 // the default, so only two workgroups ever read one line at once.
-enum WalkMode { kWalkChunk = 0, kWalkXcd = 1, kWalkPair = 2 };
+//   EVEN (pass C): contiguous chunks that differ by at most one item.  Chunks of
+// equal size leave workgroups without any: the bins of an axis are one more than
+// a power of two, so the work is often just over a whole number of items per
+// workgroup (33024 pencils at 128^3 on 1024 workgroups of 16: 2.02, of which
+// chunks of 3 keep a third of the workgroups idle).  Pass C is bound by the
+// arithmetic its waves overlap: at 96^3, 128^3 and 192^3 FP64 24.3 -> 20.4,
+// 36 -> 33 and 120 -> 116 us, at 512 x 64 x 64 48 -> 42, at 128^3 FP32 21.4 ->
+// 19.2.  The passes bound by memory gain nothing from more waves (B) or lose
+// a little (D at 256^3 FP64: 175 -> 181 us).
+enum WalkMode { kWalkChunk = 0, kWalkXcd = 1, kWalkPair = 2, kWalkEven = 3 };
 struct Walk {
     int first, last, stride;
     // the walk of workgroup g of a grid of G workgroups over `items` items
@@ -47,6 +56,11 @@ struct Walk {
             const int per = (items + 7) / 8, x = g & 7, s = g >> 3;
             const int lo = x * per, hi = lo + per < items ? lo + per : items;
             return Walk{lo + s, hi, G >> 3};
+        }
+        if (MODE == kWalkEven) {
+            const int c = items / G, r = items - c * G;
+            const int first = g * c + (g < r ? g : r);
+            return Walk{first, first + c + (g < r ? 1 : 0), 1};
         }
         const int c = (items + G - 1) / G;
         const int first = g * c;
