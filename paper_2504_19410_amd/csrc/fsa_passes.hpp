@@ -77,36 +77,31 @@ __device__ __forceinline__ void sync_wg_lds() {
 
 // The lane index, made opaque to the optimiser.  The transforms' LDS and
 // twiddle addresses depend only on it, so the compiler hoists all of them out
-// of a kernel's work loop and keeps them live for the whole loop.  Where their
-// strides do not fold into immediate offsets (lengths 3 * 2^a) and there are
-// many of them (FP64 operands, or FP32 from length 768), that overflows the
-// register file (one wave per SIMD, AGPR spills); there each work item takes
-// a fresh copy of the lane index and recomputes its addresses, at a few VALU
-// instructions per item.  Measured per evaluation: 192^3 FP64 654 -> 526 us,
-// 384^3 FP64 6.1 -> 4.2 ms, 384^3 FP32 3.46 -> 2.77 ms.  Elsewhere the
-// addresses fit and the recomputation only costs (power-of-two lengths, and
-// FP32 below 768: 192^3 FP32 263 -> 289 us, 256^3 FP32 +6%).
+// of a kernel's work loop and keeps them live for the whole loop.  Where there
+// are more than fit the registers (one wave per SIMD, AGPR spills), each work
+// item takes a fresh copy of the lane index and recomputes its addresses, at a
+// few VALU instructions per item.  That is lengths 3 * 2^a from 768 (pass C 768
+// FP64 455 -> 378 us at 384 x 192 x 192, pass D 178 -> 158 at 192 x 384 x 192,
+// pass B FP32 365 -> 311 at 384^3).  Below, the slots of a butterfly are
+// constants from its first one (Fft::pad_at), few addresses are left, and the
+// recomputation only costs (FP64 evaluations 48^3 31.2 -> 34.3 us, 96^3 60.7 ->
+// 66.0, 192^3 314 -> 323).
 __device__ __forceinline__ int opaque(int x) {
     asm volatile("" : "+v"(x));
     return x;
 }
 // Staged twiddle tables are read at every stage, at addresses of the lane too;
-// hoisted, they cost the long power-of-two transforms the same way.  There it
-// pays in pass C (FP64 from length 1024, 414 -> 360 us at 512 x
-// 512 x 64 and 97 -> 64 us at 2048^2, and FP32 at 4096, 33.0 -> 30.3 us) and
-// in passes B and D on teams of 8 operands per thread (FP64, 1024: pass D
-// 379 -> 195 us); elsewhere it costs (FP32 pass C at 1024: 134 -> 146 us).
-template <typename R, int P>
+// hoisted, they cost passes B and D on teams of 8 operands per thread the same
+// way at the long power-of-two lengths (FP64, 1024: pass D 276 -> 190 us at 512 x
+// 512 x 64).  In pass C they fit (hoisted: 2048^2 FP64 56 -> 50 us, 512 x 512 x 64
+// 353 -> 345, 1024 x 768 16.3 -> 14.7, 2048^2 FP32 30.3 -> 29.1).
+template <int P>
 constexpr bool fresh_lane() {
-    return (P & (P - 1)) != 0 && (sizeof(R) == 8 || P >= 768);
+    return (P & (P - 1)) != 0 && P >= 768;
 }
 template <typename R, class F>
 constexpr bool fresh_lane_t() {
-    return fresh_lane<R, F::P>() || (sizeof(R) == 8 && F::P >= 1024 && F::V <= 8);
-}
-template <typename R, int P>
-constexpr bool fresh_lane_conv() {
-    return fresh_lane<R, P>() || P >= (sizeof(R) == 8 ? 1024 : 4096);
+    return fresh_lane<F::P>() || (sizeof(R) == 8 && F::P >= 1024 && F::V <= 8);
 }
 
 // Whether a transposing tile of WT lines of complex values of `csize` bytes
@@ -245,7 +240,7 @@ __global__ __launch_bounds__((R2c<R, M, VAR>::THREADS)) void k_r2c(
     };
     if (ch.first < ch.last) prefetch(ch.first);
     for (int item = ch.first; item < ch.last; item += ch.stride) {
-        const int tid = fresh_lane<R, M>() ? opaque(tid0) : tid0;  // per item: fresh_lane
+        const int tid = fresh_lane<M>() ? opaque(tid0) : tid0;  // per item: fresh_lane
         int loc;
         const JobR2c jb = src.get(item, loc, cur_it);
         const int n_inner = jb.n_inner;
@@ -359,7 +354,7 @@ __global__ __launch_bounds__((C2r<R, M, VAR>::THREADS)) void k_c2r(
         if (ch.first < ch.last) prefetch(ch.first);
     }
     for (int item = ch.first; item < ch.last; item += ch.stride) {
-        const int tid = fresh_lane<R, M>() ? opaque(tid0) : tid0;  // per item: fresh_lane
+        const int tid = fresh_lane<M>() ? opaque(tid0) : tid0;  // per item: fresh_lane
         int loc;
         const JobC2r jb = src.get(item, loc, cur_it);
         const int n_inner = jb.n_inner;
@@ -729,7 +724,7 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
     };
     if constexpr (K::PREFETCH) prefetch(first);
     for (int it = 0; it < chunk; ++it) {
-        const int tid = fresh_lane_conv<R, P>() ? opaque(tid0) : tid0;  // per item: fresh_lane
+        const int tid = fresh_lane<P>() ? opaque(tid0) : tid0;  // per item: fresh_lane
         const int item = first + it * K::TPW;
         const bool active = item < total;
         int loc;
