@@ -376,7 +376,8 @@ int schedule(const fsa_plan_s* pl, int slabs, Step* out) {
 bool plane_family(const fsa_plan_s* pl, int k, int var) {
     const bool f32 = pl->prec == FSA_F32;
     const int P0 = (int)(2 * pl->N[0]);
-    return k == 2 ? conv_family(f32, P0, var) == plane_conv_alt(f32, P0) : var != 1;
+    return k == 2 ? conv_family(f32, P0, var) == plane_conv_alt(f32, P0)
+                  : var != 1 && var != 3;
 }
 
 int schedule_plane(const fsa_plan_s* pl, Step* out) {

@@ -57,7 +57,8 @@ constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 // the teams per workgroup): less LDS and fewer threads per group, more
 // resident groups per CU.  3: the default plan with the stage exchanges
 // that only trade register and lane bits done across lanes instead of
-// through the LDS (Fft::reg_exchange; the fused pass at length 512).  4:
+// through the LDS (Fft::reg_exchange; the fused pass at length 512), or, in
+// pass B in FP32 at 768, the alternate family on tiles twice as wide.  4:
 // the default plan with the first forward stage of the fused pass as a
 // matrix product on the matrix cores (FP32, length 512; Conv::MFMA0).  A
 // variant that comes out identical to variant 0 at some length is marked
@@ -419,11 +420,18 @@ __global__ __launch_bounds__((C2r<R, M, VAR>::THREADS)) void k_c2r(
 // ---------------------------------------------------------------------------
 template <typename R, int P, int VAR = 0>
 struct FwdT {
-    using F = Fft<R, P, false, var_alt(VAR)>;
+    // Variant 3: the alternate family on tiles of up to 1024 threads, whose rows
+    // are whole cache lines (FP32 at 768: 16 lines instead of 8; 127 VGPRs).
+    // On large grids the half lines of two tiles no longer meet before they go
+    // to memory (384^3: 412 -> 312 us, 256 x 384 x 256 178 -> 133); on small
+    // ones the Infinity Cache holds X2 and one workgroup per CU only costs (128 x
+    // 384 x 128 34 -> 40 us).
+    static constexpr bool WIDE = VAR == 3;
+    using F = Fft<R, P, false, WIDE ? 1 : var_alt(VAR)>;
     using C = cpx<R>;
     static constexpr int T = F::T;
-    static constexpr int WT =
-        tile_width(sizeof(C), T, F::SCR, P, var_cap(VAR, F::V <= 8 ? 1024 : 512));
+    static constexpr int WT = tile_width(sizeof(C), T, F::SCR, P,
+                                         WIDE ? 1024 : var_cap(VAR, F::V <= 8 ? 1024 : 512));
     static constexpr int TS = WT + 1;
     static constexpr int LDS = cmax(WT * F::SCR, P * TS);
     static constexpr int THREADS = WT * T;
@@ -431,7 +439,9 @@ struct FwdT {
     static constexpr int HALF = R0 / 2;
     static_assert(R0 % 2 == 0, "zero half = whole first-stage operands");
     static constexpr bool DISTINCT =
-        VAR == 0 || (VAR == 1 ? fft_alt_distinct(P) : WT != FwdT<R, P, 0>::WT);
+        VAR == 0 || (VAR == 1 ? fft_alt_distinct(P)
+                     : WIDE   ? P < 1024 && WT != FwdT<R, P, 1>::WT
+                              : WT != FwdT<R, P, 0>::WT);
 };
 
 template <typename R, int P, int VAR, class Src>

@@ -331,20 +331,26 @@ bool nearest(int prec, int key_pass, int len, int cls, Choice* out) {
 
 // The variant of an untuned (precision, pass, length): 0, except where the
 // other radix family is faster on every grid that was timed (us, variant 0 /
-// variant 1).  The lines a launch runs do not enter, so that a batch of untuned
-// problems computes bitwise what each computes alone.
+// variant 1).  The lines a launch runs choose between variants of one family at
+// most, so that a batch of untuned problems computes bitwise what each computes
+// alone.
 //   Teams of 8 operands per thread fill wider workgroups: in passes B and D
 // whole tiles of 1024 threads; in the real passes one FP64 row of 1024 no
 // longer spills (256 VGPRs and 324 bytes of scratch -> 212 VGPRs).
 //   At 768 the narrower team of family 1 (64 threads of 16 operands) doubles
 // the lines per tile, i.e. the bytes per row that passes B and D write and read.
+// In FP32 that is half a cache line; once X2 outgrows the Infinity Cache (from
+// 2^15 lines, 200 MB), pass B takes variant 3, the same family on whole lines:
+// 192 x 384 x 128 231 / 230 us, 192 x 384 x 192 360 / 349, 256 x 384 x 256 668 /
+// 580 (variant 1 / 3), but 128 x 384 x 128 146 / 154.
 //   Pass C at 128 in FP32: family 1 is 16 x 8, one exchange through the LDS
 // less.
-int default_variant(fsa_precision prec, Pass pass, int len) {
+int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
     const bool f32 = prec == FSA_F32;
     switch (pass) {
     case Pass::R2C: return !f32 && len == 1024;  // 31.3 / 20.8 (1024^2)
     case Pass::FWD_T:
+        if (f32 && len == 768 && lines >= 1 << 15) return 3;
         return len == 768                             // FP32 763 / 398, FP64 402 / 322 (384^3)
                || (f32 && (len == 1024 || len == 2048));  // 130 / 101 (512 x 512 x 64), 85 / 70
     case Pass::CONV: return f32 && len == 128;  // 22.8 / 19.6 (64 x 64 x 512)
@@ -367,7 +373,7 @@ Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched) {
     // a batched launch prefers the batched entries, then the single ones
     if (batched && nearest((int)prec, (int)pass | FSA_PASS_BATCHED, len, cls, &best)) return best;
     if (!nearest((int)prec, (int)pass, len, cls, &best))
-        best.var = default_variant(prec, pass, len);
+        best.var = default_variant(prec, pass, len, lines);
     return best;
 }
 
