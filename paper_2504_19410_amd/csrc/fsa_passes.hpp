@@ -83,7 +83,8 @@ __device__ __forceinline__ void sync_wg_lds() {
 // item takes a fresh copy of the lane index and recomputes its addresses, at a
 // few VALU instructions per item.  That is lengths 3 * 2^a from 768 (pass C 768
 // FP64 455 -> 378 us at 384 x 192 x 192, pass D 178 -> 158 at 192 x 384 x 192,
-// pass B FP32 365 -> 311 at 384^3).  Below, the slots of a butterfly are
+// pass B FP32 365 -> 311 at 384^3), except pass D in FP32, which has the registers
+// (hoisted: 330 -> 317 us at 384^3, 104 -> 100 at 128 x 768 x 128).  Below, the slots of a butterfly are
 // constants from its first one (Fft::pad_at), few addresses are left, and the
 // recomputation only costs (FP64 evaluations 48^3 31.2 -> 34.3 us, 96^3 60.7 ->
 // 66.0, 192^3 314 -> 323).
@@ -568,7 +569,7 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
         if (ch.first < ch.last) prefetch(ch.first);
     }
     for (int item = ch.first; item < ch.last; item += ch.stride) {
-        const int tid = fresh_lane_t<R, F>() ? opaque(tid0) : tid0;  // per item: fresh_lane
+        const int tid = (sizeof(R) == 8 && fresh_lane_t<R, F>()) ? opaque(tid0) : tid0;  // per item: fresh_lane
         int loc;
         const JobT jb = src.get(item, loc, cur_it);
         const int N0 = jb.N0;
