@@ -289,14 +289,15 @@ typedef enum {
  *      and lane bits of a one-wave team done across lanes (DPP and lane
  *      swaps) instead of through the LDS (the fused pass at length 512); in
  *      pass B, FP32 at length 768, the alternate family on tiles twice as wide;
+ *      in the real passes, FP64 at 768, twiddles loaded ahead of the exchanges;
  *   4  the default plan with the first forward stage of the fused pass as
  *      a matrix product on the matrix cores (FP32 MFMA; length 512).
  * and its persistent grid may use `occupancy` resident workgroups per CU
  * (0 = as many as fit).  The library keeps one process-wide table of
  * choices; untuned entries use variant 0 at full occupancy, or the variant that
  * is the faster one on every grid timed at that (precision, pass, length)
- * (fsa_tune_get reports it; by the lines only between variants 1 and 3 of pass
- * B, which compute bitwise the same).  fsa_apply, fsa_apply_batched and the
+ * (fsa_tune_get reports it; by the lines only between variants that
+ * compute bitwise the same).  fsa_apply, fsa_apply_batched and the
  * server read the table when they launch.  All
  * variants compute the same transform; results differ only by rounding.
  * On first use the table is loaded from the JSON file named by the

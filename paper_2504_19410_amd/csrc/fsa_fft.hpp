@@ -587,7 +587,11 @@ struct Fft {
     // stage s with twiddles from registers laid out like load_tw's
     template <int s, bool ZH = false>
     FSA_HD static void compute_r(C (&v)[V], int tid, const C (&w)[NTW]) {
-        constexpr int RAD = radix(s), NS = ns(s), NB = nb(s), NBT = nbt(s), OFF = tw_off(s);
+        compute_w<s, tw_off(s), ZH>(v, tid, w);
+    }
+    template <int s, int OFF, bool ZH = false, int N>
+    FSA_HD static void compute_w(C (&v)[V], int tid, const C (&w)[N]) {
+        constexpr int RAD = radix(s), NS = ns(s), NB = nb(s), NBT = nbt(s);
 #pragma unroll
         for (int b = 0; b < NBT; ++b) {
             const int j = tid + b * T;
@@ -637,16 +641,21 @@ struct Fft {
     template <int s>
     FSA_HD static void load_tw_st_from(C (&w)[NTW], int tid, const C* __restrict__ st) {
         if constexpr (s < S) {
-            constexpr int RAD = radix(s), NS = ns(s), NB = nb(s), NBT = nbt(s), OFF = tw_off(s);
-#pragma unroll
-            for (int b = 0; b < NBT; ++b) {
-                const int j = tid + b * T;
-                const int k = ((NB % T) != 0 && j >= NB) ? 0 : j % NS;
-#pragma unroll
-                for (int q = 1; q < RAD; ++q)
-                    w[OFF + b * (RAD - 1) + q - 1] = st[st_off(s) + (q - 1) * NS + k];
-            }
+            load_tw_stage<s, tw_off(s)>(w, tid, st);
             load_tw_st_from<s + 1>(w, tid, st);
+        }
+    }
+    // stage s alone, from w[OFF]
+    template <int s, int OFF, int N>
+    FSA_HD static void load_tw_stage(C (&w)[N], int tid, const C* __restrict__ st) {
+        constexpr int RAD = radix(s), NS = ns(s), NB = nb(s), NBT = nbt(s);
+#pragma unroll
+        for (int b = 0; b < NBT; ++b) {
+            const int j = tid + b * T;
+            const int k = ((NB % T) != 0 && j >= NB) ? 0 : j % NS;
+#pragma unroll
+            for (int q = 1; q < RAD; ++q)
+                w[OFF + b * (RAD - 1) + q - 1] = st[st_off(s) + (q - 1) * NS + k];
         }
     }
 
@@ -972,13 +981,22 @@ struct Fft {
         }
     }
 
-    template <int s>
+    // PRE: the stage's twiddles are asked for before the exchange, whose barriers
+    // the compiler moves no load across, and arrive behind it instead of after it
+    template <int s, bool PRE>
     static __device__ __forceinline__ void run_g_from(C (&v)[V], C* scr, int tid,
                                                       const C* __restrict__ st) {
         if constexpr (s < S) {
-            exchange<s>(v, scr, tid);
-            compute_st<s>(v, tid, st);
-            run_g_from<s + 1>(v, scr, tid, st);
+            if constexpr (PRE) {
+                C w[tw_count(s)];
+                load_tw_stage<s, 0>(w, tid, st);
+                exchange<s>(v, scr, tid);
+                compute_w<s, 0>(v, tid, w);
+            } else {
+                exchange<s>(v, scr, tid);
+                compute_st<s>(v, tid, st);
+            }
+            run_g_from<s + 1, PRE>(v, scr, tid, st);
         }
     }
 
@@ -1016,11 +1034,11 @@ struct Fft {
 
     // twiddles from the (cached) staged table, LDS-only synchronisation
     // (ZH: the upper half of every first-stage operand set is zero)
-    template <bool ZH = false>
+    template <bool ZH = false, bool PRE = false>
     static __device__ __forceinline__ void run_g(C (&v)[V], C* scr, int tid,
                                                  const C* __restrict__ st) {
         compute_st<0, ZH>(v, tid, st);
-        run_g_from<1>(v, scr, tid, st);
+        run_g_from<1, PRE>(v, scr, tid, st);
     }
 
     // run_g through a scratch of any kind (store, load), with its synchronisation:

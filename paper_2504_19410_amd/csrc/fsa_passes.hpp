@@ -58,7 +58,8 @@ constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 // resident groups per CU.  3: the default plan with the stage exchanges
 // that only trade register and lane bits done across lanes instead of
 // through the LDS (Fft::reg_exchange; the fused pass at length 512), or, in
-// pass B in FP32 at 768, the alternate family on tiles twice as wide.  4:
+// pass B in FP32 at 768, the alternate family on tiles twice as wide, in passes A
+// and E in FP64 at 768, twiddles asked for ahead of the exchanges.  4:
 // the default plan with the first forward stage of the fused pass as a
 // matrix product on the matrix cores (FP32, length 512; Conv::MFMA0).  A
 // variant that comes out identical to variant 0 at some length is marked
@@ -194,8 +195,17 @@ struct R2c {
     static constexpr int R0 = F::first_radix(), NB0 = F::first_stride(), NBT0 = F::first_nbt();
     static constexpr int HALF = R0 / 2;
     static_assert(R0 % 2 == 0, "zero half = whole first-stage operands");
+    // Twiddles ahead of the exchanges (Fft::run_g) where the table is read: FP64
+    // 2048^2 41.4 -> 40.1 and (pass E) 39.7 -> 38.6 us, 64 x 64 x 1024 36.0 -> 33.5 and
+    // 34.1 -> 32.6.  At 768 in FP64 they cost one of two workgroups per CU (127 ->
+    // 160 VGPRs), which only launches of at most one workgroup per CU do not miss
+    // (1024 x 768 20.9 -> 17.9 and 12.7 -> 9.3; 192 x 64 x 768 76 -> 83 and 83 -> 92):
+    // variant 3 has them there.
+    static constexpr bool PRE = VAR == 3 || !(sizeof(R) == 8 && M == 768);
     static constexpr bool DISTINCT =
-        VAR == 0 || (VAR == 1 ? fft_alt_distinct(M) : WT != R2c<R, M, 0>::WT);
+        VAR == 0 || (VAR == 1   ? fft_alt_distinct(M)
+                     : VAR == 3 ? sizeof(R) == 8 && M == 768
+                                : WT != R2c<R, M, 0>::WT);
 };
 
 template <typename R, int M, int VAR, class Src>
@@ -257,7 +267,7 @@ __global__ __launch_bounds__((R2c<R, M, VAR>::THREADS)) void k_r2c(
                 v[b * K::R0 + q] = (q < K::HALF && active) ? pf[b * K::HALF + q] : mk(R(0), R(0));
         if (item + ch.stride < ch.last) prefetch(item + ch.stride);
         if constexpr (F::REG_TW) F::template run_r<true>(v, scr, tid, w);
-        else F::template run_g<true>(v, scr, tid, st);
+        else F::template run_g<true, K::PRE>(v, scr, tid, st);
         F::store_last(v, tid, M, [&](int k, C z) { scr[F::pad(k)] = z; });
         F::sync_lds();
         C x[K::NX];
@@ -315,8 +325,11 @@ struct C2r {
     static constexpr bool PREFETCH =
         NT * (int)(sizeof(C) / 4) <= 48 && !(sizeof(R) == 4 && F::V >= 16 && M >= 2048);
     static constexpr int R0 = F::first_radix(), NB0 = F::first_stride(), NBT0 = F::first_nbt();
+    static constexpr bool PRE = R2c<R, M, VAR>::PRE;
     static constexpr bool DISTINCT =
-        VAR == 0 || (VAR == 1 ? fft_alt_distinct(M) : WT != C2r<R, M, 0>::WT);
+        VAR == 0 || (VAR == 1   ? fft_alt_distinct(M)
+                     : VAR == 3 ? sizeof(R) == 8 && M == 768
+                                : WT != C2r<R, M, 0>::WT);
 };
 
 template <typename R, int M, int VAR, class Src>
@@ -392,7 +405,7 @@ __global__ __launch_bounds__((C2r<R, M, VAR>::THREADS)) void k_c2r(
         });
         sync_wg_lds();
         if constexpr (F::REG_TW) F::run_r(v, scr, tid, w);
-        else F::run_g(v, scr, tid, st);
+        else F::template run_g<false, K::PRE>(v, scr, tid, st);
         const int inner = col0 + team;
         if (inner < n_inner) {
             const size_t r0 = ((size_t)outer * n_inner + inner) * M;
@@ -642,6 +655,12 @@ struct Conv {
     // 2D batch's fused pass at 2048: 490 -> 428 us; at 4096 the kernel stays
     // at two waves either way and keeps the prefetch)
     static constexpr bool PREFETCH = !(sizeof(R) == 4 && Ff::V >= 16 && P <= 2048);
+    // Twiddles ahead of the exchanges (Fft::run_g) where the table is read and they
+    // cost no resident wave: FP32 (384^3 563 -> 556 us), FP64 of 3 * 2^a from 1536
+    // (768 x 96 x 48: 99 -> 87).  FP64 at 768 goes from 4 waves per SIMD to 3 (380 ->
+    // 402 us at 384 x 192 x 192), the powers of two from 2 to 1 (1024: 42 -> 49 at 512 x
+    // 64 x 64, 4096: 52 -> 66 at 2048^2).
+    static constexpr bool PRE = sizeof(R) == 4 || (P % 3 == 0 && P >= 1536);
     static_assert(R0 % 2 == 0, "the zero half must be whole first-stage operands");
     static_assert(Ff::last_radix() == Fi::first_radix(), "register hand-off");
     // Variant 4: the first forward stage as a matrix product on the matrix
@@ -793,12 +812,12 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
                 Ff::template run_r_from<2>(v, scr, tid, wf);
             } else {
                 Ff::template compute_st<1>(v, tid, stf);
-                Ff::template run_g_from<2>(v, scr, tid, stf);
+                Ff::template run_g_from<2, K::PRE>(v, scr, tid, stf);
             }
         } else if constexpr (REG) {
             Ff::template run_r<true>(v, scr, tid, wf);
         } else {
-            Ff::template run_g<true>(v, scr, tid, stf);
+            Ff::template run_g<true, K::PRE>(v, scr, tid, stf);
         }
         {
             int i = 0;
@@ -806,7 +825,7 @@ __global__ __launch_bounds__((Conv<R, P, VAR>::THREADS)) void k_conv(
         }
         if constexpr (REG && K::SHARED_TW) Fi::run_r(v, scr, tid, wf);
         else if constexpr (REG) Fi::run_r(v, scr, tid, wi);
-        else Fi::run_g(v, scr, tid, sti);
+        else Fi::template run_g<false, K::PRE>(v, scr, tid, sti);
         if (active) {
             C* pen = (C*)jb.data + (size_t)qp * N0;
             Fi::store_last(v, tid, N0, [&](int i, C c) { pen[i] = c; });

@@ -342,13 +342,17 @@ bool nearest(int prec, int key_pass, int len, int cls, Choice* out) {
 // In FP32 that is half a cache line; once X2 outgrows the Infinity Cache (from
 // 2^15 lines, 200 MB), pass B takes variant 3, the same family on whole lines:
 // 192 x 384 x 128 231 / 230 us, 192 x 384 x 192 360 / 349, 256 x 384 x 256 668 /
-// 580 (variant 1 / 3), but 128 x 384 x 128 146 / 154.
+// 580 (variant 1 / 3), but 128 x 384 x 128 146 / 154.  The real passes of 768 in
+// FP64 take variant 3 while every workgroup (4 rows) has a CU of its own: 1024 x 768
+// 43.8 / 36.0 us, 32 x 32 x 768 46.5 / 40.6, but 192 x 64 x 768 466 / 477 (variant 0 / 3).
 //   Pass C at 128 in FP32: family 1 is 16 x 8, one exchange through the LDS
 // less.
 int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
     const bool f32 = prec == FSA_F32;
     switch (pass) {
-    case Pass::R2C: return !f32 && len == 1024;  // 31.3 / 20.8 (1024^2)
+    case Pass::R2C:
+        if (!f32 && len == 768 && lines <= 1024) return 3;
+        return !f32 && len == 1024;  // 31.3 / 20.8 (1024^2)
     case Pass::FWD_T:
         if (f32 && len == 768 && lines >= 1 << 15) return 3;
         return len == 768                             // FP32 763 / 398, FP64 402 / 322 (384^3)
@@ -359,6 +363,7 @@ int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
                || (f32 ? len == 2048                  // 104 / 96 (128 x 1024 x 64)
                        : len == 1024);                // 261 / 195 (512 x 512 x 64)
     case Pass::C2R:
+        if (!f32 && len == 768 && lines <= 1024) return 3;
         return f32 ? len == 384                       // 184 / 155 (384^3)
                    : len == 1024 || len == 2048;      // 16.0 / 10.2 (1024^2), 59.5 / 40.6
     }
