@@ -639,7 +639,15 @@ struct Conv {
     using Fi = Fft<R, P, true, ALT, var_xch(VAR)>;
     using C = cpx<R>;
     static constexpr int T = Ff::T;
-    static constexpr int TPW = cmax(1, var_cap(VAR, 256) / T);  // teams per workgroup
+    // Teams per workgroup: 256 threads, variant 2 half of them.  Teams of two waves
+    // meet at the workgroup's barrier, where two teams only wait for each other:
+    // there variant 0 takes one team a workgroup and variant 2 two (FP32 768 555 ->
+    // 527 us at 384^3, 146 -> 139 at 384 x 384 x 96; 2048 76 -> 74 at 1024 x 128 x
+    // 64, 12 -> 11 at 1024^2; FP64 2048 188 -> 180, 20 -> 17.5).  The FP64 teams of
+    // 3 * 2^a keep two (768: 376 against 380 us at 384 x 192 x 192, 260 against 266 at
+    // 384 x 384 x 64; 1536: 99 against 114 at 768 x 96 x 48).
+    static constexpr bool SOLO = T == 128 && (sizeof(R) == 4 || P == 2048);
+    static constexpr int TPW = cmax(1, (SOLO != (VAR == 2) ? 128 : 256) / T);
     static constexpr int THREADS = TPW * T;
     static constexpr int LDS = TPW * Ff::SCR;
     static constexpr bool SHARED_TW = Ff::palindromic();
