@@ -1019,8 +1019,10 @@ struct Fft {
     static __device__ __forceinline__ void run_g_split_from(C (&v)[V], R* scr, int tid,
                                                             const C* __restrict__ st) {
         if constexpr (s < S) {
+            C w[tw_count(s)];  // ahead of the exchange (run_g_from)
+            load_tw_stage<s, 0>(w, tid, st);
             exchange_split<s>(v, scr, tid);
-            compute_st<s>(v, tid, st);
+            compute_w<s, 0>(v, tid, w);
             run_g_split_from<s + 1>(v, scr, tid, st);
         }
     }
@@ -1047,11 +1049,13 @@ struct Fft {
     static __device__ __forceinline__ void run_x_from(C (&v)[V], Scr scr, int tid,
                                                       const C* __restrict__ st, Sync&& sync) {
         if constexpr (s < S) {
+            C w[tw_count(s)];  // ahead of the exchange (run_g_from)
+            load_tw_stage<s, 0>(w, tid, st);
             store<s - 1>(v, scr, tid);
             sync();
             load<s>(v, scr, tid);
             sync();
-            compute_st<s>(v, tid, st);
+            compute_w<s, 0>(v, tid, w);
             run_x_from<s + 1>(v, scr, tid, st, sync);
         }
     }

@@ -109,7 +109,7 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec_row(
         Ff::load_first(x, tid, P, [&](int t) {
             return act ? mk(((const R*)in)[rb + t], R(0)) : mk(R(0), R(0));
         });
-        Ff::run_g(x, sc, tid, Ff::staged(tw));
+        Ff::template run_g<false, true>(x, sc, tid, Ff::staged(tw));
         if (act)
             Ff::store_last(x, tid, P, [&](int t, C c) {
                 if (t < H) ((C*)out)[ro + t] = c;
@@ -120,7 +120,7 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec_row(
             if (!act) return mk(R(0), R(0));
             return t < H ? ((const C*)in)[rb + t] : conj(((const C*)in)[rb + P - t]);
         });
-        Fi::run_g(x, sc, tid, Fi::staged(tw));
+        Fi::template run_g<false, true>(x, sc, tid, Fi::staged(tw));
         if (act) Fi::store_last(x, tid, P, [&](int t, C c) { ((R*)out)[ro + t] = c.x; });
     }
 }
@@ -133,7 +133,9 @@ __global__ __launch_bounds__((Spec<R, P>::THREADS)) void k_spec_row(
 // of 128 bytes: no bank is met twice).
 // At 128^3 FP64 launches 1-3 take 10.3, 14.5 and 10.3 us (34 MB each: 3.3 TB/s);
 // with the tile staged through the LDS before and after, its loads one after
-// another, they took 17.6, 20.1 and 17.6.
+// another, they took 17.6, 20.1 and 17.6.  A stage's twiddles are loaded ahead of
+// its exchange (Fft::run_x; the five launches 152 -> 143 us at 256^3 FP32, 126 ->
+// 121 at 192^3 FP64).
 template <class C, int W>
 struct Column {  // a team's scratch: entry i of column w of [i][W]
     C* p;
