@@ -224,21 +224,23 @@ fsa_status fsa_build_tensor(fsa_plan pl, void* stream) {
         return fail(FSA_ESTATE, "fsa_build_tensor: plan was built on device %d, current is %d",
                     pl->device, dev);
     const size_t rsize = pl->csize / 2;
-    if (!pl->tensor) {
-        e = hipMalloc(&pl->tensor, pl->tensor_elems * rsize);
+    if (!pl->block) {
+        // tensor, twiddles and line order in one allocation: each more costs a build
+        // and a destroy some 10 us of host time, about a launch of the evaluation
+        auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+        const size_t tb = up(pl->tensor_elems * rsize), wb = up(pl->tw_elems * pl->csize);
+        const bool order = pl->d == 3 && pl->prec != FSA_DD;
+        const size_t ob = order ? sizeof(int) * (size_t)(pl->N[1] + 1) * (pl->N[2] + 1) : 0;
+        e = hipMalloc(&pl->block, tb + wb + ob);
         if (e != hipSuccess) {
-            pl->tensor = nullptr;
+            pl->block = nullptr;
             return fail(FSA_ENOMEM, "fsa_build_tensor: tensor allocation (%zu bytes): %s",
-                        pl->tensor_elems * rsize, hipGetErrorString(e));
+                        tb + wb + ob, hipGetErrorString(e));
         }
-    }
-    if (!pl->twiddles) {
-        e = hipMalloc(&pl->twiddles, pl->tw_elems * pl->csize);
-        if (e != hipSuccess) {
-            pl->twiddles = nullptr;
-            return fail(FSA_ENOMEM, "fsa_build_tensor: twiddle allocation: %s",
-                        hipGetErrorString(e));
-        }
+        pl->device = dev;
+        pl->tensor = pl->block;
+        pl->twiddles = (char*)pl->block + tb;
+        if (order) pl->line_order = (int*)((char*)pl->block + tb + wb);
     }
     if (pl->prec == FSA_DD) {
         e = fsa::build_tensor_dd(pl, st);
@@ -253,7 +255,7 @@ fsa_status fsa_build_tensor(fsa_plan pl, void* stream) {
     e = fsa::build_twiddles(pl->prec, pl->tws, pl->n_tws, pl->twiddles, st);
     if (e != hipSuccess) return hip_fail(e, "fsa_build_tensor: twiddle kernels");
     e = fsa::build_tensor_device(pl->kp, pl->d, pl->L, pl->N, pl->h, pl->prec, pl->tensor,
-                                 &pl->line_order, st);
+                                 !pl->built, pl->line_order, &pl->line_order_built, st);
     if (e == hipErrorOutOfMemory)
         return fail(FSA_ENOMEM, "fsa_build_tensor: temporary FP64 octant: %s",
                     hipGetErrorString(e));
@@ -581,19 +583,11 @@ fsa_status fsa_plan_destroy(fsa_plan pl) {
     if (!pl) return FSA_OK;
     fsa::batch_forget_plan(pl->id);
     hipError_t e = hipSuccess;
-    if (pl->tensor || pl->twiddles || pl->line_order) {
+    if (pl->block) {
         int cur = 0;
         (void)hipGetDevice(&cur);
         if (pl->device >= 0 && pl->device != cur) (void)hipSetDevice(pl->device);
-        if (pl->tensor) e = hipFree(pl->tensor);
-        if (pl->twiddles) {
-            hipError_t e2 = hipFree(pl->twiddles);
-            if (e == hipSuccess) e = e2;
-        }
-        if (pl->line_order) {
-            hipError_t e2 = hipFree(pl->line_order);
-            if (e == hipSuccess) e = e2;
-        }
+        e = hipFree(pl->block);
         if (pl->device >= 0 && pl->device != cur) (void)hipSetDevice(cur);
     }
     delete pl;

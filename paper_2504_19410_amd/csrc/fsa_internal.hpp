@@ -73,13 +73,15 @@ hipError_t build_tensor_dd(const fsa_plan_s* pl, hipStream_t st);
 hipError_t launch_dd_step(const fsa_plan_s* pl, int k, const void* rho, void* phi, void* ws,
                           hipStream_t st);
 
-// Tensor generation (fsa_tensor.hip).  line_order: the caller's cache of the
+// Tensor generation (fsa_tensor.hip).  line_order: the caller's array of the
 // order in which the last axis of a 3D build takes its lines (it depends on
-// the grid sizes only): filled with a new device allocation by the first build
-// that uses it, reused after that, freed by the caller.
+// the grid sizes only): filled by the first build that uses it, which sets
+// *line_order_built, and reused after that.  first: nothing reads tensor_out yet,
+// so the build may use it for an intermediate octant.
 hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, const int64_t* N,
                                const double* h, fsa_precision prec, void* tensor_out,
-                               int** line_order, hipStream_t st);
+                               bool first, int* line_order, bool* line_order_built,
+                               hipStream_t st);
 // Twiddle tables of a length n at out + off (elements): the plain one
 // (tw[m] = exp(-2 pi i m / n), m in [0, n)) or, staged, all kTwTables of them
 // (fsa_fft.hpp), computed in FP64, stored in prec; one launch for all lengths,
@@ -301,8 +303,10 @@ struct fsa_plan_s {
     double dn[3] = {0, 0, 0}, dm[3] = {0, 0, 0};
     // device state
     int device = -1;
+    void* block = nullptr;  // the one allocation that holds the following
     void* tensor = nullptr;
     void* twiddles = nullptr;
-    int* line_order = nullptr;  // the tensor build's line order (3D cubic boxes), kept
+    int* line_order = nullptr;  // 3D: the tensor build's line order (cubic boxes), kept
+    bool line_order_built = false;
     bool built = false;
 };

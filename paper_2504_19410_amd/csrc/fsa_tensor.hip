@@ -841,7 +841,8 @@ hipError_t build_twiddles(fsa_precision prec, const TwTables* tables, int count,
 
 hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, const int64_t* N,
                                const double* h, fsa_precision prec, void* tensor_out,
-                               int** line_order, hipStream_t st) {
+                               bool first, int* line_order, bool* line_order_built,
+                               hipStream_t st) {
     // octant extents D_j = N_j + 1, axis 0 innermost; a 2D plan has D2 = 1
     const long D0 = N[0] + 1, D1 = N[1] + 1, D2 = d == 3 ? N[2] + 1 : 1;
     const long n = D0 * D1 * D2;
@@ -849,11 +850,6 @@ hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, c
     WTable wt{nullptr, 0.0, 0};
     std::vector<void*> wbufs;
     hipError_t e = kp.general ? build_w_table(kp, d, L, N, st, &wt, &wbufs) : hipSuccess;
-    // intermediate octants between the axes: one for 2D, two for 3D
-    double *a = nullptr, *b = nullptr;
-    void* tw = nullptr;
-    if (e == hipSuccess) e = hipMallocAsync((void**)&a, sizeof(double) * n, st);
-    if (e == hipSuccess && d == 3) e = hipMallocAsync((void**)&b, sizeof(double) * n, st);
     // twiddles of every axis
     TwTables tws[3] = {};
     size_t tw_n = 0;
@@ -861,8 +857,6 @@ hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, c
         tws[j] = TwTables{tw_n, (int)(2 * N[j]), true};
         tw_n += (size_t)kTwTables * 2 * N[j];
     }
-    if (e == hipSuccess) e = hipMallocAsync(&tw, sizeof(cpx<double>) * tw_n, st);
-    if (e == hipSuccess) e = build_twiddles(FSA_F64, tws, d, tw, st);
     DctEnds ends{};
     ends.kp = kp;
     double prodP = 1.0;
@@ -886,34 +880,49 @@ hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, c
     }
     const long ntab = msum + 1;
     const bool small = ntab * 4 <= n;
-    double *t1_tab = nullptr, *w_tab = nullptr;
-    if (e == hipSuccess && small && same_h) {
-        e = hipMallocAsync((void**)&t1_tab, sizeof(double) * ntab, st);
-        if (e == hipSuccess)
-            e = launch_kernel(k_radial<true>, dim3((unsigned)((ntab + 255) / 256)), dim3(256), 0,
-                              st, t1_tab, ntab, h[0], ends);
+    // One scratch allocation: the intermediate octants between the axes (one for 2D,
+    // two for 3D, of which a first FP64 build keeps the one that its last axis does
+    // not read where the tensor will be), the twiddles and the tables.
+    char* scratch = nullptr;
+    size_t bytes = 0;
+    auto take = [&](size_t b) {
+        const size_t at = bytes;
+        bytes += (b + 255) & ~size_t(255);
+        return at;
+    };
+    const bool in_out = d == 3 && prec == FSA_F64 && first;
+    const size_t at_a = in_out ? 0 : take(sizeof(double) * n);
+    const size_t at_b = d == 3 ? take(sizeof(double) * n) : 0;
+    const size_t at_tw = take(sizeof(cpx<double>) * tw_n);
+    const size_t at_t1 = small && same_h ? take(sizeof(double) * ntab) : 0;
+    const size_t at_w = small && same_c ? take(sizeof(double) * ntab) : 0;
+    if (e == hipSuccess) e = hipMallocAsync((void**)&scratch, bytes, st);
+    double *a = nullptr, *b = nullptr, *t1_tab = nullptr, *w_tab = nullptr;
+    void* tw = nullptr;
+    if (e == hipSuccess) {
+        a = in_out ? (double*)tensor_out : (double*)(scratch + at_a);
+        if (d == 3) b = (double*)(scratch + at_b);
+        tw = scratch + at_tw;
+        if (small && same_h) t1_tab = (double*)(scratch + at_t1);
+        if (small && same_c) w_tab = (double*)(scratch + at_w);
+        e = build_twiddles(FSA_F64, tws, d, tw, st);
     }
-    if (e == hipSuccess && small && same_c) {
-        e = hipMallocAsync((void**)&w_tab, sizeof(double) * ntab, st);
-        if (e == hipSuccess)
-            e = launch_kernel(k_radial<false>, dim3((unsigned)((ntab + 255) / 256)), dim3(256), 0,
-                              st, w_tab, ntab, ends.c[0], ends);
-    }
+    if (e == hipSuccess && t1_tab)
+        e = launch_kernel(k_radial<true>, dim3((unsigned)((ntab + 255) / 256)), dim3(256), 0, st,
+                          t1_tab, ntab, h[0], ends);
+    if (e == hipSuccess && w_tab)
+        e = launch_kernel(k_radial<false>, dim3((unsigned)((ntab + 255) / 256)), dim3(256), 0, st,
+                          w_tab, ntab, ends.c[0], ends);
     ends.t1_tab = t1_tab;
     ends.w_tab = w_tab;
     // the order of the rows of axis 0, where the last axis (axis 0) of a 3D
     // build reads W from the radial table: computed once, kept by the caller
-    if (e == hipSuccess && w_tab && d == 3 && !*line_order) {
-        int* order = nullptr;
-        e = hipMalloc((void**)&order, sizeof(int) * D1 * D2);
-        if (e == hipSuccess) {
-            e = launch_kernel(k_row_order, dim3((unsigned)((D1 * D2 * kRankLanes + 255) / 256)),
-                              dim3(256), 0, st, order, (int)D1, (int)D2);
-            if (e == hipSuccess) *line_order = order;
-            else (void)hipFree(order);
-        }
+    if (e == hipSuccess && w_tab && d == 3 && !*line_order_built) {
+        e = launch_kernel(k_row_order, dim3((unsigned)((D1 * D2 * kRankLanes + 255) / 256)),
+                          dim3(256), 0, st, line_order, (int)D1, (int)D2);
+        *line_order_built = e == hipSuccess;
     }
-    int* rows = w_tab && d == 3 ? *line_order : nullptr;
+    int* rows = w_tab && d == 3 ? line_order : nullptr;
     // lines along axis ax; groups take lines adjacent in memory (or, on
     // axis 0, in the order of rows)
     auto lines = [&](int ax) {
@@ -944,12 +953,8 @@ hipError_t build_tensor_device(const KernelParams& kp, int d, const double* L, c
                 : w_tab ? dct_axis<DctStage::LAST, double, true>(last_in, nullptr, ln, nn, atw, ends, st)
                         : dct_axis<DctStage::LAST, double, false>(last_in, nullptr, ln, nn, atw, ends, st);
     }
-    if (t1_tab) (void)hipFreeAsync(t1_tab, st);
-    if (w_tab) (void)hipFreeAsync(w_tab, st);
     for (void* p : wbufs) (void)hipFreeAsync(p, st);
-    if (a) (void)hipFreeAsync(a, st);
-    if (b) (void)hipFreeAsync(b, st);
-    if (tw) (void)hipFreeAsync(tw, st);
+    if (scratch) (void)hipFreeAsync(scratch, st);
     return e;
 }
 
