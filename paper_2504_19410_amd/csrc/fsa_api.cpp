@@ -375,11 +375,8 @@ int schedule(const fsa_plan_s* pl, int slabs, Step* out) {
     return m;
 }
 
-bool plane_family(const fsa_plan_s* pl, int k, int var) {
-    const bool f32 = pl->prec == FSA_F32;
-    const int P0 = (int)(2 * pl->N[0]);
-    return k == 2 ? conv_family(f32, P0, var) == plane_conv_alt(f32, P0)
-                  : var != 1 && var != 3;
+bool plane_family(int k, int var) {
+    return var != 1 && (k == 2 || var != 3);
 }
 
 int schedule_plane(const fsa_plan_s* pl, Step* out) {
@@ -388,9 +385,9 @@ int schedule_plane(const fsa_plan_s* pl, Step* out) {
     const bool f32 = pl->prec == FSA_F32;
     if (!(f32 ? PlaneV<float>::fits(P1, P0) : PlaneV<double>::fits(P1, P0))) return 0;
     // only where it computes what the launches chosen for the passes compute:
-    // the default radix family in passes B and D, plane_conv_alt's in pass C
+    // the default radix family
     for (int k = 1; k <= 3; ++k)
-        if (!plane_family(pl, k, step_choice(pl, Step{k, 0, H}).var)) return 0;
+        if (!plane_family(k, step_choice(pl, Step{k, 0, H}).var)) return 0;
     int m = 0;
     for (int i = 0; i < pl->n_spectral; ++i) out[m++] = Step{kSpectralStep + i, 0, 0};
     out[m++] = Step{0, 0, H};

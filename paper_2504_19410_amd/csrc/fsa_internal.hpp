@@ -254,7 +254,7 @@ int schedule(const fsa_plan_s* pl, int slabs, Step* out);
 // (0: it does not; `schedule` then gives the launches).
 int schedule_plane(const fsa_plan_s* pl, Step* out);
 // Whether variant var of pass k (1 .. 3) computes what that launch computes.
-bool plane_family(const fsa_plan_s* pl, int k, int var);
+bool plane_family(int k, int var);
 hipError_t launch_step(const fsa_plan_s* pl, const Step& s, const void* rho, void* phi, void* ws,
                        Choice c, hipStream_t st);
 Choice step_choice(const fsa_plan_s* pl, const Step& s);

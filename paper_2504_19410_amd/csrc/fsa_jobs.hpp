@@ -35,20 +35,6 @@ struct JobPlane {  // passes B, C, D (3D) of small planes in one launch
     int H;               // bins p2
 };
 
-// Radix family of pass C at variant var (fsa_passes.hpp, Conv): at length 256 in
-// FP32 variant 0 is 16 x 16 (one exchange through the LDS) and variant 1 is
-// 8 x 4 x 8 (two); 19.4 against 23.5 us at 128^3, 32.4 against 39.4 at 128 x 128
-// x 256, equal at 128 x 1024 x 64.  In FP64 16 operands per thread cost what the
-// exchange saves.
-constexpr int conv_family(bool f32, int P0, int var) {
-    const int alt = var == 1 ? 1 : 0;
-    return f32 && P0 == 256 ? 1 - alt : alt;
-}
-// ... and in the small-plane launch: the one pass C's own untuned launch takes.
-constexpr int plane_conv_alt(bool f32, int P0) {
-    return conv_family(f32, P0, f32 && P0 == 128 ? 1 : 0);
-}
-
 enum class Pass { R2C = 0, FWD_T = 1, CONV = 2, INV_T = 3, C2R = 4 };
 
 }  // namespace fsa

@@ -634,7 +634,7 @@ __global__ __launch_bounds__((InvT<R, P, VAR>::THREADS)) void k_inv_t(
 // ---------------------------------------------------------------------------
 template <typename R, int P, int VAR = 0>
 struct Conv {
-    static constexpr int ALT = conv_family(sizeof(R) == 4, P, VAR);
+    static constexpr int ALT = var_alt(VAR);
     using Ff = Fft<R, P, false, ALT, var_xch(VAR)>;
     using Fi = Fft<R, P, true, ALT, var_xch(VAR)>;
     using C = cpx<R>;

@@ -31,11 +31,10 @@ constexpr int kPlaneValues = 2 * 2048;  // N0 P1
 template <typename R, int P1, int P0>
 struct Plane {
     using C = cpx<R>;
-    static constexpr int ALT0 = plane_conv_alt(sizeof(R) == 4, P0);
     using F1 = Fft<R, P1, false>;  // pass B
     using I1 = Fft<R, P1, true>;   // pass D
-    using F0 = Fft<R, P0, false, ALT0>;  // pass C
-    using I0 = Fft<R, P0, true, ALT0>;
+    using F0 = Fft<R, P0, false>;  // pass C
+    using I0 = Fft<R, P0, true>;
     static constexpr int N1 = P1 / 2, N0 = P0 / 2;
     static constexpr int T1 = F1::T, T0 = F0::T;
     // threads: at least 8 values of the plane each, within 64 .. 1024 (with 16

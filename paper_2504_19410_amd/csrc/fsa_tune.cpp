@@ -345,8 +345,9 @@ bool nearest(int prec, int key_pass, int len, int cls, Choice* out) {
 // 580 (variant 1 / 3), but 128 x 384 x 128 146 / 154.  The real passes of 768 in
 // FP64 take variant 3 while every workgroup (4 rows) has a CU of its own: 1024 x 768
 // 43.8 / 36.0 us, 32 x 32 x 768 46.5 / 40.6, but 192 x 64 x 768 466 / 477 (variant 0 / 3).
-//   Pass C at 128 in FP32: family 1 is 16 x 8, one exchange through the LDS
-// less.
+//   Close calls stay with variant 0: what family 1 gains on large grids it loses
+// on small ones (FP32 pass E 384 162 / 155 us at 384^3 but 5.8 / 7.9 at 256 x 384,
+// pass C 128 19.5 / 19.8 at 64 x 64 x 512 and 5.0 / 6.1 at 64^2).
 int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
     const bool f32 = prec == FSA_F32;
     switch (pass) {
@@ -357,15 +358,14 @@ int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
         if (f32 && len == 768 && lines >= 1 << 15) return 3;
         return len == 768                             // FP32 763 / 398, FP64 402 / 322 (384^3)
                || (f32 && (len == 1024 || len == 2048));  // 130 / 101 (512 x 512 x 64), 85 / 70
-    case Pass::CONV: return f32 && len == 128;  // 22.8 / 19.6 (64 x 64 x 512)
+    case Pass::CONV: return 0;
     case Pass::INV_T:
         return len == 768                             // FP32 488 / 336, FP64 354 / 292 (384^3)
                || (f32 ? len == 2048                  // 104 / 96 (128 x 1024 x 64)
                        : len == 1024);                // 261 / 195 (512 x 512 x 64)
     case Pass::C2R:
         if (!f32 && len == 768 && lines <= 1024) return 3;
-        return f32 ? len == 384                       // 184 / 155 (384^3)
-                   : len == 1024 || len == 2048;      // 16.0 / 10.2 (1024^2), 59.5 / 40.6
+        return !f32 && (len == 1024 || len == 2048);  // 16.0 / 10.2 (1024^2), 59.5 / 40.6
     }
     return 0;
 }
@@ -697,7 +697,7 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
                 size_t w = 0, f = cands_of[k].size();
                 for (size_t c = 0; c < cands_of[k].size(); ++c) {
                     if (us_of[k][c] < us_of[k][w]) w = c;
-                    if (fsa::plane_family(pl, k, cands_of[k][c].var) &&
+                    if (fsa::plane_family(k, cands_of[k][c].var) &&
                         (f == cands_of[k].size() || us_of[k][c] < us_of[k][f]))
                         f = c;
                 }
