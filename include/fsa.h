@@ -284,7 +284,8 @@ typedef enum {
  *   0  default radix plan and workgroup size;
  *   1  alternate radix family (another radix split and number of threads
  *      per transform);
- *   2  half-size workgroups (half the lines per tile, or teams per group);
+ *   2  half-size workgroups (half the lines per tile, or teams per group; the
+ *      fused pass's teams of two waves default to one a group: two);
  *   3  the default plan with the stage exchanges that only trade register
  *      and lane bits of a one-wave team done across lanes (DPP and lane
  *      swaps) instead of through the LDS (the fused pass at length 512); in
