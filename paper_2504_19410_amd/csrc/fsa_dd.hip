@@ -16,12 +16,12 @@
 //           crop folded into the loads and stores.
 // rho and phi are real, so the last axis keeps only its bins 0 .. N_last (the
 // others are conjugates), and its transforms take two rows in one complex FFT.
-// A workgroup of 256 threads transforms W = 1024 / P lines (at least one) with a
-// radix-4 FFT in LDS, neighbouring lines side by side: every wave is full and
-// the strided axes are read in runs of W values.  The arithmetic bounds it (a
-// double-double addition is 20 FP64 operations, a product 10): 64^3 took 342 us
-// on the whole complex spectrum with one line per workgroup of P / 4 threads
-// (half a wave at P = 128), 159 us this way; its fused pass 186 us, now 81.
+// A workgroup transforms W neighbouring lines (dd_lines) with a radix-4 FFT in LDS:
+// every wave is full and the strided axes are read in runs of W values.  A thread
+// stays with one line, so its addresses cost one division each.  The arithmetic
+// bounds it (a double-double addition is 20 FP64 operations, a product 10): 64^3
+// took 344 us on the whole complex spectrum with one line per workgroup of P / 4
+// threads (half a wave at P = 128), 163 us this way; its fused pass 186 us, now 76.
 // Arrays of reals are interleaved (hi, lo) pairs; complex values are
 // (re.hi, re.lo, im.hi, im.lo).
 #include <hip/hip_runtime.h>
@@ -44,11 +44,19 @@ __device__ __forceinline__ cdd cmul(cdd a, cdd b) {
 }
 __device__ __forceinline__ cdd cconj(cdd a) { return cdd{a.re, -a.im}; }
 
-constexpr int kDDThreads = 256;
-constexpr int kDDMaxP = 2048;
-// lines per workgroup: one radix-4 butterfly per thread and step, where the line
-// is short enough
-constexpr int dd_lines(int P) { return P >= 4 * kDDThreads ? 1 : 4 * kDDThreads / P; }
+// Thread tid's place in its workgroup's W lines: a line has dd_line_threads(P)
+// threads, neighbours of one line (rows, contiguous) or of W lines side by side
+// (strided axes, where neighbouring lines are neighbours in memory).
+struct DDThread {
+    int w, t, n;  // line; first element; threads per line (a power of two)
+    __device__ __forceinline__ DDThread(bool rows, int W, int P) {
+        n = dd_line_threads(P);
+        const int tid = (int)threadIdx.x;
+        const int logn = 31 - __clz(n), logw = 31 - __clz(W);
+        w = rows ? tid >> logn : tid & (W - 1);
+        t = rows ? tid & (n - 1) : tid >> logw;
+    }
+};
 
 // tw[m] = exp(-2 pi i m / P), m < P/2
 __global__ void k_dd_twiddle(cdd* __restrict__ tw, int P) {
@@ -163,7 +171,7 @@ template <bool INV>
 __device__ void dd_fft_lds(const DDTile& x, int W, int P, int logP, const cdd* __restrict__ tw) {
     int len = 4;
     if (logP & 1) {
-        for (int b = threadIdx.x; b < W * (P / 2); b += kDDThreads) {
+        for (int b = threadIdx.x; b < W * (P / 2); b += blockDim.x) {
             const cdd u = x.get(2 * b), v = x.get(2 * b + 1);
             x.put(2 * b, cadd(u, v));
             x.put(2 * b + 1, csub(u, v));
@@ -171,7 +179,7 @@ __device__ void dd_fft_lds(const DDTile& x, int W, int P, int logP, const cdd* _
         __syncthreads();
         len = 8;
     } else {  // groups of four points: every twiddle is 1
-        for (int b = threadIdx.x; b < W * (P / 4); b += kDDThreads) {
+        for (int b = threadIdx.x; b < W * (P / 4); b += blockDim.x) {
             const cdd a0 = x.get(4 * b), a1 = x.get(4 * b + 1);
             const cdd a2 = x.get(4 * b + 2), a3 = x.get(4 * b + 3);
             const cdd b0 = cadd(a0, a1), b1 = csub(a0, a1);
@@ -187,7 +195,7 @@ __device__ void dd_fft_lds(const DDTile& x, int W, int P, int logP, const cdd* _
     }
     for (int lq = (logP & 1) ? 1 : 2; len <= P; len <<= 2, lq += 2) {
         const int q = len >> 2, step = P / len;  // q = 2^lq divides P / 4
-        for (int b = threadIdx.x; b < W * (P / 4); b += kDDThreads) {
+        for (int b = threadIdx.x; b < W * (P / 4); b += blockDim.x) {
             const int g = b >> lq, j = b & (q - 1);
             const int i0 = g * len + j;
             const cdd w2 = INV ? cconj(tw[2 * j * step]) : tw[2 * j * step];
@@ -215,13 +223,15 @@ __device__ __forceinline__ int bitrev(int t, int logP) {
 // DCT-I along axis ax of the octant (D_j = N_j + 1 points per axis), as the
 // real part of the length-2N DFT of each line's even extension (x[m] for
 // m <= N, x[2N - m] above): sum_m c_m x[m] cos(pi p m / N), c_0 = c_N = 1,
-// else 2.  W lines per workgroup; tw: the axis' twiddles of length 2N.
+// else 2.  W lines (a power of two) per workgroup; tw: the axis' twiddles of
+// length 2N.
 __global__ __launch_bounds__(kDDThreads) void k_dd_dct(const dd* __restrict__ in,
                                                      dd* __restrict__ out, DDGeom g, int ax,
-                                                     long lines, const cdd* __restrict__ tw) {
+                                                     long lines, int W,
+                                                     const cdd* __restrict__ tw) {
     extern __shared__ dd lds[];
     const int D0 = g.N[0] + 1, D1 = g.d > 1 ? g.N[1] + 1 : 1;
-    const int N = g.N[ax], P = 2 * N, W = dd_lines(P);
+    const int N = g.N[ax], P = 2 * N;
     const DDTile x{lds, lds + W * P};
     int logP = 0;
     while ((1 << logP) < P) ++logP;
@@ -231,20 +241,18 @@ __global__ __launch_bounds__(kDDThreads) void k_dd_dct(const dd* __restrict__ in
         if (ax == 1) return (l / D0) * (long)D1 * D0 + l % D0;            // l = a2 D0 + a0
         return l;                                                         // l = a1 D0 + a0
     };
-    const long l0 = (long)blockIdx.x * W;
-    for (int e = threadIdx.x; e < W * P; e += kDDThreads) {
-        // neighbours in memory on neighbouring threads
-        const int w = ax == 0 ? e / P : e % W, t = ax == 0 ? e % P : e / W;
+    const DDThread th(ax == 0, W, P);
+    const long l = (long)blockIdx.x * W + th.w;
+    const bool act = l < lines;
+    const long b = act ? base(l) : 0;
+    for (int t = th.t; t < P; t += th.n) {
         const int m = t <= N ? t : P - t;
-        x.put(w * P + bitrev(t, logP),
-              cdd{l0 + w < lines ? in[base(l0 + w) + m * stride] : dd_of(0.0), dd_of(0.0)});
+        x.put(th.w * P + bitrev(t, logP), cdd{act ? in[b + m * stride] : dd_of(0.0), dd_of(0.0)});
     }
     __syncthreads();
     dd_fft_lds<false>(x, W, P, logP, tw);
-    for (int e = threadIdx.x; e < W * (N + 1); e += kDDThreads) {
-        const int w = ax == 0 ? e / (N + 1) : e % W, p = ax == 0 ? e % (N + 1) : e / W;
-        if (l0 + w < lines) out[base(l0 + w) + p * stride] = x.re[w * P + p];
-    }
+    if (act)
+        for (int p = th.t; p <= N; p += th.n) out[b + p * stride] = x.re[th.w * P + p];
 }
 
 // Where a line lives: element t of line l is at base(l) + t * es, with
@@ -270,106 +278,98 @@ struct DDConv {  // octant lookup of T^ along axis-0 lines at (p1, p2)
 template <int MODE>
 __global__ __launch_bounds__(kDDThreads) void k_dd_pass(const void* __restrict__ in,
                                                         void* __restrict__ out, DDLines li,
-                                                        DDLines lo, long lines, int P, int logP,
-                                                        int n_in, int n_out,
+                                                        DDLines lo, long lines, int W, int P,
+                                                        int logP, int n_in, int n_out,
                                                         const cdd* __restrict__ tw, DDConv cv) {
     extern __shared__ dd lds[];
-    const int W = dd_lines(P);
     const DDTile x{lds, lds + W * P};
-    const long l0 = (long)blockIdx.x * W;
-    for (int e = threadIdx.x; e < W * P; e += kDDThreads) {
+    constexpr bool REAL = MODE == DD_FWD_REAL || MODE == DD_INV_REAL;
+    const DDThread th(REAL, W, P);
+    const int xw = th.w * P;
+    const long line = (long)blockIdx.x * W + th.w;
+    const bool act = line < lines;
+    // bases of the line, or of its two rows
+    const long l0 = act ? (REAL ? 2 * line : line) : 0, l1 = REAL && act ? l0 + 1 : l0;
+    const long ia = li.base(l0), ib = li.base(l1), oa = lo.base(l0), ob = lo.base(l1);
+    for (int t = th.t; t < P; t += th.n) {
         cdd v = cdd{dd_of(0.0), dd_of(0.0)};
-        int w, t;
-        if constexpr (MODE == DD_FWD_REAL || MODE == DD_INV_REAL) {  // contiguous rows
-            w = e / P;
-            t = e % P;
-        } else {  // neighbouring lines are neighbours in memory
-            w = e % W;
-            t = e / W;
-        }
-        if (l0 + w < lines) {
+        if (act) {
             if constexpr (MODE == DD_FWD_REAL) {
                 if (t < n_in) {
-                    v.re = ((const dd*)in)[li.base(2 * (l0 + w)) + t];
-                    v.im = ((const dd*)in)[li.base(2 * (l0 + w) + 1) + t];
+                    v.re = ((const dd*)in)[ia + t];
+                    v.im = ((const dd*)in)[ib + t];
                 }
             } else if constexpr (MODE == DD_INV_REAL) {
                 // Z[k] = A[k] + i B[k], Z[P-k] = conj A[k] + i conj B[k]
                 const int k = t <= P / 2 ? t : P - t;
-                cdd a = ((const cdd*)in)[li.base(2 * (l0 + w)) + k];
-                cdd b = ((const cdd*)in)[li.base(2 * (l0 + w) + 1) + k];
+                cdd a = ((const cdd*)in)[ia + k];
+                cdd b = ((const cdd*)in)[ib + k];
                 if (t > P / 2) {
                     a = cconj(a);
                     b = cconj(b);
                 }
                 v = cdd{a.re - b.im, a.im + b.re};
             } else {
-                if (t < n_in) v = ((const cdd*)in)[li.base(l0 + w) + t * li.es];
+                if (t < n_in) v = ((const cdd*)in)[ia + t * li.es];
             }
         }
-        x.put(w * P + bitrev(t, logP), v);
+        x.put(xw + bitrev(t, logP), v);
     }
     __syncthreads();
     if constexpr (MODE == DD_CONV) {
         dd_fft_lds<false>(x, W, P, logP, tw);
+        // neighbours of one line: T^ and the tile are contiguous along it
+        const DDThread tr(true, W, P);
+        const int rw = tr.w * P;
+        const long l = (long)blockIdx.x * W + tr.w, ln = l < lines ? l : 0;
+        // line at (p1, p2), p2 <= N_2, in 3D; p1 <= N_1 in 2D
+        int a1 = (int)ln, a2 = 0;
+        if (cv.d == 3) {
+            const int p1 = (int)(ln / (cv.N[2] + 1));
+            a2 = (int)(ln - (long)p1 * (cv.N[2] + 1));
+            a1 = p1 <= cv.N[1] ? p1 : cv.P[1] - p1;
+        }
+        const dd* trow = cv.tensor + ((long)a2 * cv.D1 + a1) * cv.D0;
         // x (natural order) times T^, back into bit-reversed order for the
         // inverse: every product is formed before any is written back
         // (fixed trip counts keep the array in registers)
-        constexpr int kKeep = kDDMaxP / kDDThreads;  // W P / kDDThreads <= 8
+        constexpr int kKeep = kDDMaxP / kDDThreads;  // P / dd_line_threads(P) <= 8
         cdd keep[kKeep];
 #pragma unroll
         for (int r = 0; r < kKeep; ++r) {
-            const int e = threadIdx.x + r * kDDThreads;
-            const int w = e / P, t = e % P;
-            if (e < W * P && l0 + w < lines) {
-                // line at (p1, p2), p2 <= N_2, in 3D; p1 <= N_1 in 2D
-                const long line = l0 + w;
-                int a1, a2 = 0;
-                if (cv.d == 3) {
-                    const int p1 = (int)(line / (cv.N[2] + 1));
-                    a2 = (int)(line % (cv.N[2] + 1));
-                    a1 = p1 <= cv.N[1] ? p1 : cv.P[1] - p1;
-                } else {
-                    a1 = (int)line;
-                }
+            const int t = tr.t + r * tr.n;
+            if (t < P) {
                 const int a0 = t <= cv.N[0] ? t : P - t;
-                const dd s = cv.tensor[((long)a2 * cv.D1 + a1) * cv.D0 + a0];
-                cdd v = x.get(e);
+                const dd s = trow[a0];
+                cdd v = x.get(rw + t);
                 v.re = v.re * s;
                 v.im = v.im * s;
                 keep[r] = v;
-            } else {
-                keep[r] = cdd{dd_of(0.0), dd_of(0.0)};
             }
         }
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kKeep; ++r) {
-            const int e = threadIdx.x + r * kDDThreads;
-            if (e < W * P) x.put((e / P) * P + bitrev(e % P, logP), keep[r]);
+            const int t = tr.t + r * tr.n;
+            if (t < P) x.put(rw + bitrev(t, logP), keep[r]);
         }
         __syncthreads();
     }
     if constexpr (MODE == DD_FWD || MODE == DD_FWD_REAL) dd_fft_lds<false>(x, W, P, logP, tw);
     else dd_fft_lds<true>(x, W, P, logP, tw);
-    for (int e = threadIdx.x; e < W * n_out; e += kDDThreads) {
-        if constexpr (MODE == DD_FWD_REAL || MODE == DD_INV_REAL) {
-            const int w = e / n_out, t = e % n_out;
-            if (l0 + w >= lines) continue;
-            const long ba = lo.base(2 * (l0 + w)) + t, bb = lo.base(2 * (l0 + w) + 1) + t;
-            const cdd z = x.get(w * P + t);
-            if constexpr (MODE == DD_FWD_REAL) {
-                const cdd c = cconj(x.get(w * P + (t == 0 ? 0 : P - t)));
-                const cdd a = cadd(z, c), b = csub(z, c);
-                ((cdd*)out)[ba] = cdd{a.re * 0.5, a.im * 0.5};
-                ((cdd*)out)[bb] = cdd{b.im * 0.5, -(b.re * 0.5)};
-            } else {
-                ((dd*)out)[ba] = z.re;
-                ((dd*)out)[bb] = z.im;
-            }
+    if (!act) return;
+    for (int t = th.t; t < n_out; t += th.n) {
+        const cdd z = x.get(xw + t);
+        if constexpr (MODE == DD_FWD_REAL) {
+            const cdd c = cconj(x.get(xw + (t == 0 ? 0 : P - t)));
+            const cdd a = cadd(z, c), b = csub(z, c);
+            ((cdd*)out)[oa + t] = cdd{a.re * 0.5, a.im * 0.5};
+            ((cdd*)out)[ob + t] = cdd{b.im * 0.5, -(b.re * 0.5)};
+        } else if constexpr (MODE == DD_INV_REAL) {
+            ((dd*)out)[oa + t] = z.re;
+            ((dd*)out)[ob + t] = z.im;
         } else {
-            const int w = e % W, t = e / W;
-            if (l0 + w < lines) ((cdd*)out)[lo.base(l0 + w) + t * lo.es] = x.get(w * P + t);
+            ((cdd*)out)[oa + t * lo.es] = z;
         }
     }
 }
@@ -422,10 +422,10 @@ hipError_t build_tensor_dd(const fsa_plan_s* pl, hipStream_t st) {
         for (int ax = 0; ax < pl->d; ++ax) {
             const int P = 2 * g.N[ax];
             const long lines = n / (g.N[ax] + 1);
-            const int W = dd_lines(P);
-            hipLaunchKernelGGL(k_dd_dct, dim3((unsigned)((lines + W - 1) / W)), dim3(kDDThreads),
-                               sizeof(cdd) * (size_t)(W * P), st, (const dd*)src, dst, g, ax,
-                               lines, dd_tw(pl, ax));
+            const int W = dd_lines(P, lines, device_cus());
+            hipLaunchKernelGGL(k_dd_dct, dim3((unsigned)((lines + W - 1) / W)),
+                               dim3(W * dd_line_threads(P)), sizeof(cdd) * (size_t)(W * P), st,
+                               (const dd*)src, dst, g, ax, lines, W, dd_tw(pl, ax));
             dd* t = src;
             src = dst;
             dst = t;
@@ -439,8 +439,9 @@ hipError_t build_tensor_dd(const fsa_plan_s* pl, hipStream_t st) {
     return e;
 }
 
-// Step k of a double-double evaluation (2d - 1 launches).  X holds the padded
-// spectrum's bins 0 .. N_last of the last axis, C order (P_0, ..., N_last + 1).
+// Step k of a double-double evaluation (2d - 1 launches).  X holds bins 0 .. N_last
+// of the last axis, C order: (N_0, P_1, N_2 + 1) in 3D, (N_0, N_1 + 1) in 2D (the
+// fused pass pads and crops axis 0 in LDS).
 hipError_t launch_dd_step(const fsa_plan_s* pl, int k, const void* rho, void* phi, void* ws,
                           hipStream_t st) {
     const int d = pl->d;
@@ -540,28 +541,28 @@ hipError_t launch_dd_step(const fsa_plan_s* pl, int k, const void* rho, void* ph
         }
     }
     if (Pa > kDDMaxP || lines <= 0 || lines > 0x7fffffffL) return hipErrorInvalidValue;
-    const int W = dd_lines(Pa);
-    const dim3 grid((unsigned)((lines + W - 1) / W)), block(kDDThreads);
+    const int W = dd_lines(Pa, lines, device_cus());
+    const dim3 grid((unsigned)((lines + W - 1) / W)), block(W * dd_line_threads(Pa));
     const size_t lds = sizeof(cdd) * (size_t)(W * Pa);
     const cdd* tw = dd_tw(pl, ax);
     const void* src = mode == DD_FWD_REAL ? rho : (const void*)X;
     void* dst = mode == DD_INV_REAL ? phi : (void*)X;
     switch (mode) {
     case DD_FWD_REAL:
-        return launch_kernel(k_dd_pass<DD_FWD_REAL>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
-                             lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_FWD_REAL>, grid, block, lds, st, src, dst, li, lo, lines, W,
+                             Pa, lg, n_in, n_out, tw, cv);
     case DD_FWD:
-        return launch_kernel(k_dd_pass<DD_FWD>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
-                             lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_FWD>, grid, block, lds, st, src, dst, li, lo, lines, W,
+                             Pa, lg, n_in, n_out, tw, cv);
     case DD_CONV:
-        return launch_kernel(k_dd_pass<DD_CONV>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
-                             lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_CONV>, grid, block, lds, st, src, dst, li, lo, lines, W,
+                             Pa, lg, n_in, n_out, tw, cv);
     case DD_INV:
-        return launch_kernel(k_dd_pass<DD_INV>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
-                             lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_INV>, grid, block, lds, st, src, dst, li, lo, lines, W,
+                             Pa, lg, n_in, n_out, tw, cv);
     default:
-        return launch_kernel(k_dd_pass<DD_INV_REAL>, grid, block, lds, st, src, dst, li, lo, lines, Pa,
-                             lg, n_in, n_out, tw, cv);
+        return launch_kernel(k_dd_pass<DD_INV_REAL>, grid, block, lds, st, src, dst, li, lo, lines, W,
+                             Pa, lg, n_in, n_out, tw, cv);
     }
 }
 

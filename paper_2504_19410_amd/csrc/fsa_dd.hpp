@@ -29,6 +29,23 @@
 
 namespace fsa {
 
+// Shape of a launch of the double-double transforms: threads per line of length P
+// (one radix-4 butterfly each and step, where the line is short enough) and lines
+// per workgroup, of up to 256 threads.  A launch of fewer workgroups than CUs takes
+// fewer lines in each, down to one wave: its time is one workgroup's, and the waves
+// of a CU share what each of them then has alone (64 x 64 39.9 us with one line of
+// 32 threads per workgroup, 48.3 with groups of 256 threads, 36.4 with this rule;
+// 8 x 8 x 8 43.2, 46.9, 37.3; half a wave: 40.9 and 38.9).
+constexpr int kDDThreads = 256;
+constexpr int kDDMaxP = 2048;
+constexpr int dd_line_threads(int P) { return P >= 4 * kDDThreads ? kDDThreads : P / 4; }
+constexpr int dd_lines(int P, long lines, int cus) {
+    const int n = dd_line_threads(P);
+    int W = kDDThreads / n;
+    while (W * n > 64 && W > 1 && (lines + W - 1) / W < cus) W /= 2;
+    return W;
+}
+
 struct dd {
     double hi, lo;
 };

@@ -95,6 +95,19 @@ constexpr int kMaxTwLengths = 6;
 hipError_t build_twiddles(fsa_precision prec, const TwTables* tables, int count, void* out,
                           hipStream_t st);
 
+// Compute units of the current device (the library drives one device).
+inline int device_cus() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            n <= 0)
+            n = 256;
+        return n;
+    }();
+    return cus;
+}
+
 // Launch configuration of one pass: compile-time variant (0 default, 1
 // alternate radix family, 2 half-size workgroups, 3 exchanges across lanes,
 // 4 first stage on the matrix cores)

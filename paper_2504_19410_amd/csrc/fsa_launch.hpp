@@ -15,19 +15,6 @@
 
 namespace fsa {
 
-// Compute units of the current device (the library drives one device).
-inline int device_cus() {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            n <= 0)
-            n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 // Resident workgroups per CU of a kernel at a block size.
 template <typename Kern>
 int blocks_per_cu(Kern kernel, int threads) {
