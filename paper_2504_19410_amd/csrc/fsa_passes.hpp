@@ -326,6 +326,10 @@ struct C2r {
         NT * (int)(sizeof(C) / 4) <= 48 && !(sizeof(R) == 4 && F::V >= 16 && M >= 2048);
     static constexpr int R0 = F::first_radix(), NB0 = F::first_stride(), NBT0 = F::first_nbt();
     static constexpr bool PRE = R2c<R, M, VAR>::PRE;
+    // FP32 rows of 24 take 171 VGPRs when nothing is asked, three more than let a third
+    // wave reside; held to 168 they spill 20 bytes (192 x 192 x 24: 51.9 -> 47.7 us,
+    // this pass 8.9 -> 7.7; the launches of one item per workgroup 0.1 us slower).
+    static constexpr int WAVES = VAR == 0 && sizeof(R) == 4 && M == 24 ? 3 : 0;  // 0: not asked
     static constexpr bool DISTINCT =
         VAR == 0 || (VAR == 1   ? fft_alt_distinct(M)
                      : VAR == 3 ? sizeof(R) == 8 && M == 768
@@ -333,7 +337,7 @@ struct C2r {
 };
 
 template <typename R, int M, int VAR, class Src>
-__global__ __launch_bounds__((C2r<R, M, VAR>::THREADS)) void k_c2r(
+__global__ __launch_bounds__((C2r<R, M, VAR>::THREADS), (C2r<R, M, VAR>::WAVES)) void k_c2r(
     Src src, const cpx<R>* __restrict__ twM, const cpx<R>* __restrict__ tw2M) {
     using K = C2r<R, M, VAR>;
     using F = typename K::F;
