@@ -383,7 +383,7 @@ int schedule_plane(const fsa_plan_s* pl, Step* out) {
     if (pl->d != 3 || pl->prec == FSA_DD || tune::get_slabs(pl) != 1) return 0;
     const int P0 = (int)(2 * pl->N[0]), P1 = (int)(2 * pl->N[1]), H = (int)pl->H;
     const bool f32 = pl->prec == FSA_F32;
-    if (!(f32 ? PlaneV<float>::fits(P1, P0) : PlaneV<double>::fits(P1, P0))) return 0;
+    if (!(f32 ? PlaneV<float>::faster(P1, P0, H) : PlaneV<double>::faster(P1, P0, H))) return 0;
     // only where it computes what the launches chosen for the passes compute:
     // the default radix family
     for (int k = 1; k <= 3; ++k)

@@ -156,6 +156,8 @@ struct PlaneV {
                              hipStream_t st);
     // Whether a plane of these padded lengths fits a workgroup.
     static bool fits(int P1, int P0);
+    // Whether H of them are faster than the passes apart, where nothing was tuned.
+    static bool faster(int P1, int P0, int H);
 };
 
 // Dispatch on the run-time choice.

@@ -37,8 +37,8 @@ struct Plane {
     using I0 = Fft<R, P0, true>;
     static constexpr int N1 = P1 / 2, N0 = P0 / 2;
     static constexpr int T1 = F1::T, T0 = F0::T;
-    // threads: at least 8 values of the plane each, within 64 .. 1024 (with 16
-    // values each 32^3 FP32 takes 15.2 us instead of 13.5, with 4 14.0)
+    // threads: a power of two from 64, at least 8 values of the plane each beyond 64
+    // (with 16 values each 32^3 FP32 takes 15.2 us instead of 13.5, with 4 14.0)
     static constexpr int VPT = 8;
     static constexpr int threads() {
         int t = 64;
@@ -58,6 +58,18 @@ struct Plane {
     // FP32 keeps the twiddles of both axes in registers
     static constexpr bool REG = sizeof(R) == 4;
     static_assert(F0::last_radix() == I0::first_radix(), "register hand-off");
+    // operands a thread takes through the stages of pass B and of pass C one after
+    // another (pass D and the inverse of C repeat them)
+    static constexpr int CHAIN = RB * F1::V * F1::S + RC * F0::V * F0::S;
+    // Planes whose workgroup is slower than the three launches while few of them run
+    // side by side: in FP64, long chains.  One launch / apart, us: 12 x 96 at N_2 = 8,
+    // 32, 64, 96 22.5 / 20.3, 23.9 / 21.0, 24.2 / 22.6, 29.8 / 30.6; 96 x 16 20.3 /
+    // 20.0, 21.6 / 20.0, 22.0 / 21.9, 27.7 / 31; 24 x 64 at 16, 32, 48, 64 21.3 / 20.5,
+    // 21.5 / 21.1, 27.4 / 27.5, 21.9 / 23.1.  The others gain in a stream at every N_2
+    // (64 x 32, chain 64, at N_2 = 8: 18.2 / 19.6), where five launches take 20 us at
+    // least; replayed from a graph, where that is 16, some lose at N_2 = 8 (17.9 / 16.0).
+    static constexpr bool FEW_SLOW = sizeof(R) == 8 && N0 * N1 > 1024 && CHAIN >= 120;
+    static constexpr int FEW = cmax(P0, P1) >= 192 ? 96 : 64;
 };
 
 template <typename R, int P1, int P0>

@@ -49,4 +49,19 @@ bool PlaneV<R>::fits(int P1, int P0) {
     return false;
 }
 
+template <typename R>
+bool PlaneV<R>::faster(int P1, int P0, int H) {
+    switch (P1 * 4096 + P0) {
+#define FSA_CASE(p1, p0) \
+    case p1 * 4096 + p0: \
+        return Plane<R, p1, p0>::FITS && \
+               !(Plane<R, p1, p0>::FEW_SLOW && H < Plane<R, p1, p0>::FEW);
+#define FSA_ROW(p1) FSA_PLANE_P_LIST(FSA_CASE, p1)
+        FSA_PLANE_ROWS(FSA_ROW)
+#undef FSA_ROW
+#undef FSA_CASE
+    }
+    return false;
+}
+
 }  // namespace fsa
