@@ -349,7 +349,9 @@ fsa_status fsa_tune_get(int precision, int pass, int length, int64_t lines, int*
  * spectrum can stay in the device's memory-side cache between them (slabs = 1:
  * each pass over the whole grid).  Same results for every slab count.
  * N: the three grid lengths.  fsa_autotune times 1, 2, 4, 8, 16 slabs after
- * tuning the passes.  `us` (may be NULL) receives the measured evaluation
+ * tuning the passes, and on small planes B, C and D in one launch, and keeps
+ * which was faster with the slabs (in the file: "one_launch", 0 or 1; a count
+ * set by hand leaves that to the library).  `us` (may be NULL) receives the measured evaluation
  * time of the chosen schedule (0 if set by hand or untuned). */
 fsa_status fsa_tune_set_slabs(int precision, const int64_t* N, int slabs);
 fsa_status fsa_tune_get_slabs(int precision, const int64_t* N, int* slabs, double* us);

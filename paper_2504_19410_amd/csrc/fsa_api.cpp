@@ -379,21 +379,45 @@ bool plane_family(int k, int var) {
     return var != 1 && (k == 2 || var != 3);
 }
 
-int schedule_plane(const fsa_plan_s* pl, Step* out) {
-    if (pl->d != 3 || pl->prec == FSA_DD || tune::get_slabs(pl) != 1) return 0;
-    const int P0 = (int)(2 * pl->N[0]), P1 = (int)(2 * pl->N[1]), H = (int)pl->H;
-    const bool f32 = pl->prec == FSA_F32;
-    if (!(f32 ? PlaneV<float>::faster(P1, P0, H) : PlaneV<double>::faster(P1, P0, H))) return 0;
-    // only where it computes what the launches chosen for the passes compute:
-    // the default radix family
-    for (int k = 1; k <= 3; ++k)
-        if (!plane_family(k, step_choice(pl, Step{k, 0, H}).var)) return 0;
+static bool plane_fits(const fsa_plan_s* pl) {
+    if (pl->d != 3 || pl->prec == FSA_DD) return false;
+    const int P0 = (int)(2 * pl->N[0]), P1 = (int)(2 * pl->N[1]);
+    return pl->prec == FSA_F32 ? PlaneV<float>::fits(P1, P0) : PlaneV<double>::fits(P1, P0);
+}
+
+int plane_steps(const fsa_plan_s* pl, Step* out) {
+    if (!plane_fits(pl)) return 0;
+    const int H = (int)pl->H;
     int m = 0;
     for (int i = 0; i < pl->n_spectral; ++i) out[m++] = Step{kSpectralStep + i, 0, 0};
     out[m++] = Step{0, 0, H};
     out[m++] = Step{kPlaneStep, 0, H};
     out[m++] = Step{4, 0, H};
     return m;
+}
+
+bool runs_plane(const fsa_plan_s* pl) {
+    int one = -1;
+    if (!plane_fits(pl) || tune::get_slabs(pl, &one) != 1 || one == 0) return false;
+    const int H = (int)pl->H;
+    // a variant that the launch does not compute: set by hand, it is wanted; tuned,
+    // it is the faster one apart, unless the grid itself was tuned to one launch
+    for (int k = 1; k <= 3; ++k) {
+        Pass pass;
+        int len;
+        pass_of(pl, k, &pass, &len);
+        tune::From from;
+        const Choice c = tune::get(pl->prec, pass, len, step_lines(pl, Step{k, 0, H}), false, &from);
+        if (!plane_family(k, c.var) && (one < 0 || from == tune::From::kByHand)) return false;
+    }
+    if (one == 1) return true;
+    const int P0 = (int)(2 * pl->N[0]), P1 = (int)(2 * pl->N[1]);
+    return pl->prec == FSA_F32 ? PlaneV<float>::faster(P1, P0, H)
+                               : PlaneV<double>::faster(P1, P0, H);
+}
+
+int schedule_plane(const fsa_plan_s* pl, Step* out) {
+    return runs_plane(pl) ? plane_steps(pl, out) : 0;
 }
 
 long step_lines(const fsa_plan_s* pl, const Step& s) {
@@ -410,12 +434,18 @@ long step_lines(const fsa_plan_s* pl, const Step& s) {
     return s.k == 1 ? (long)pl->H : N0;     // 2D: pencils, else rows
 }
 
-Choice step_choice(const fsa_plan_s* pl, const Step& s) {
+Choice table_choice(const fsa_plan_s* pl, const Step& s) {
     if (s.k >= kSpectralStep || pl->prec == FSA_DD) return Choice{};
     Pass pass;
     int len;
     pass_of(pl, s.k, &pass, &len);
     return tune::get(pl->prec, pass, len, step_lines(pl, s));
+}
+
+Choice step_choice(const fsa_plan_s* pl, const Step& s) {
+    const Choice c = table_choice(pl, s);
+    const bool middle = pl->d == 3 && s.k >= 1 && s.k <= 3;
+    return middle && !plane_family(s.k, c.var) && runs_plane(pl) ? Choice{} : c;
 }
 
 // Enqueues one evaluation: pass A, then passes B, C, D per slab of bins p2

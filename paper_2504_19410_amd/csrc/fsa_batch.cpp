@@ -61,6 +61,12 @@ struct Group {
     std::vector<int> start{0};
     size_t job_size = 0;
     int n = 0;
+    // per job: its transforms, and whether fsa_apply runs the pass within one launch
+    // of passes B, C and D (a choice outside that launch's radix family would give
+    // other bits)
+    std::vector<long> job_lines;
+    std::vector<bool> plane;
+    bool family = false;  // all jobs do, and the table's choice is outside it
 };
 
 struct Entry {
@@ -86,10 +92,11 @@ constexpr size_t kCacheCap = 16;
 // Adds one problem's job to its (pass, length, precision) group.  Returns
 // false for an unsupported length.
 template <class Job>
-bool add_job(std::map<std::tuple<int, int, int>, Group>& groups, fsa::Pass pass, int len,
-             fsa_precision prec, const void* tw, const void* tw2, const Job& job, long lines) {
+bool add_job(std::map<std::tuple<int, int, int, int>, Group>& groups, fsa::Pass pass, int len,
+             fsa_precision prec, const void* tw, const void* tw2, const Job& job, long lines,
+             bool plane) {
     if (!fft_length_ok(pass, len)) return false;
-    Group& g = groups[std::make_tuple((int)pass, len, (int)prec)];
+    Group& g = groups[std::make_tuple((int)pass, len, (int)prec, 0)];
     if (g.n == 0) {
         g.pass = pass;
         g.len = len;
@@ -101,6 +108,8 @@ bool add_job(std::map<std::tuple<int, int, int>, Group>& groups, fsa::Pass pass,
     const unsigned char* p = (const unsigned char*)&job;
     g.jobs.insert(g.jobs.end(), p, p + sizeof(Job));
     g.lines += lines;
+    g.job_lines.push_back(lines);
+    g.plane.push_back(plane);
     ++g.n;
     return true;
 }
@@ -154,7 +163,56 @@ hipError_t launch_group(const Group& g, const char* tables, hipStream_t st) {
                                                           total, g.tw, g.tw2, g.ch, st);
 }
 
-using Groups = std::map<std::tuple<int, int, int>, Group>;
+using Groups = std::map<std::tuple<int, int, int, int>, Group>;
+
+// The table's choice for a group.
+fsa::Choice group_choice(const Group& g) {
+    return g.family ? fsa::Choice{} : fsa::tune::get(g.prec, g.pass, g.len, g.lines, true);
+}
+
+// Where single-evaluation entries give a group a choice outside the radix family of
+// the one launch of B, C and D, the jobs of plans that run that launch get a group of
+// their own on variant 0, and each problem computes what it computes alone.
+void split_planes(Groups& groups) {
+    Groups apart;
+    for (auto it = groups.begin(); it != groups.end();) {
+        Group& g = it->second;
+        const auto key = it->first;
+        fsa::tune::From from;
+        const fsa::Choice c = fsa::tune::get(g.prec, g.pass, g.len, g.lines, true, &from);
+        if (from == fsa::tune::From::kBatched || fsa::plane_family((int)g.pass, c.var) ||
+            std::find(g.plane.begin(), g.plane.end(), true) == g.plane.end()) {
+            ++it;
+            continue;
+        }
+        Group part[2];
+        for (int f = 0; f < 2; ++f) {
+            part[f].pass = g.pass;
+            part[f].len = g.len;
+            part[f].prec = g.prec;
+            part[f].tw = g.tw;
+            part[f].tw2 = g.tw2;
+            part[f].job_size = g.job_size;
+            part[f].family = f == 1;
+        }
+        for (int i = 0; i < g.n; ++i) {
+            Group& p = part[g.plane[i] ? 1 : 0];
+            const unsigned char* job = g.jobs.data() + (size_t)i * g.job_size;
+            p.jobs.insert(p.jobs.end(), job, job + g.job_size);
+            p.job_lines.push_back(g.job_lines[i]);
+            p.plane.push_back(g.plane[i]);
+            p.lines += g.job_lines[i];
+            ++p.n;
+        }
+        it = groups.erase(it);
+        for (int f = 0; f < 2; ++f)
+            if (part[f].n > 0)
+                apart.emplace(std::make_tuple(std::get<0>(key), std::get<1>(key),
+                                              std::get<2>(key), f),
+                              std::move(part[f]));
+    }
+    groups.merge(apart);
+}
 
 // Sorts the problems' jobs into (pass, length, precision) groups; the
 // launch choices are not fixed yet.
@@ -173,8 +231,12 @@ fsa_status make_groups(int n, const fsa_plan* plans, const void* const* rho, voi
         char* w2 = w1 + align256(pl->ws1_elems * cs);
         ws += align256(pl->ws_bytes);
         const fsa_precision pr = pl->prec;
+        const bool plane = fsa::runs_plane(pl);
         auto add = [&](auto job, fsa::Pass pass, int len, const void* t1, const void* t2,
-                       long lines) { return add_job(groups, pass, len, pr, t1, t2, job, lines); };
+                       long lines) {
+            const bool middle = pass != fsa::Pass::R2C && pass != fsa::Pass::C2R;
+            return add_job(groups, pass, len, pr, t1, t2, job, lines, plane && middle);
+        };
         const long n0 = N0, n1 = N1, h = H;
         bool ok;
         if (pl->d == 3) {
@@ -198,6 +260,7 @@ fsa_status make_groups(int n, const fsa_plan* plans, const void* const* rho, voi
             return FSA_EUNSUPPORTED;
         }
     }
+    split_planes(groups);
     return FSA_OK;
 }
 
@@ -208,7 +271,7 @@ fsa_status build_entry(int n, const fsa_plan* plans, const void* const* rho, voi
     if (st != FSA_OK) return st;
     for (auto& kv : groups) {
         Group& g = kv.second;
-        finish_group(g, fsa::tune::get(g.prec, g.pass, g.len, g.lines, true));
+        finish_group(g, group_choice(g));
     }
     // one device buffer: per group [jobs | start], each part 256-byte aligned
     size_t bytes = 0;
@@ -452,7 +515,7 @@ fsa_status fsa_autotune_batched(int n, const fsa_plan* plans, const void* const*
     size_t fixed_bytes = 0, trial_bytes = 0;
     std::vector<size_t> offs;
     for (Group* g : order) {
-        finish_group(*g, fsa::tune::get(g->prec, g->pass, g->len, g->lines, true));
+        finish_group(*g, group_choice(*g));
         offs.push_back(fixed_bytes);
         fixed_bytes += table_bytes(*g);
         trial_bytes = std::max(trial_bytes, table_bytes(*g));

@@ -240,8 +240,11 @@ struct Launch {
 namespace tune {
 int size_class(long lines);
 // `batched`: the entries of the batched persistent launches (a batched get
-// falls back to the single-evaluation entries where it has none).
-Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched = false);
+// falls back to the single-evaluation entries where it has none).  from: where the
+// choice comes from.
+enum class From { kUntuned, kByHand, kMeasured, kBatched };
+Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched = false,
+           From* from = nullptr);
 void set(fsa_precision prec, Pass pass, int len, long lines, Choice c, double us,
          bool batched = false);
 // Bumped on every change; batch graphs captured under another generation
@@ -268,11 +271,22 @@ int schedule(const fsa_plan_s* pl, int slabs, Step* out);
 // The same with passes B, C and D in one launch, where fsa_apply runs them so
 // (0: it does not; `schedule` then gives the launches).
 int schedule_plane(const fsa_plan_s* pl, Step* out);
+// The launches themselves, where the planes fit (0: they do not).
+int plane_steps(const fsa_plan_s* pl, Step* out);
+// Whether fsa_apply runs them so.
+bool runs_plane(const fsa_plan_s* pl);
 // Whether variant var of pass k (1 .. 3) computes what that launch computes.
 bool plane_family(int k, int var);
 hipError_t launch_step(const fsa_plan_s* pl, const Step& s, const void* rho, void* phi, void* ws,
                        Choice c, hipStream_t st);
+// The table's choice for a step, and the one it is launched with: a pass of a plan
+// that runs B, C and D in one launch takes variant 0 where the table names another
+// radix family, so that it computes the same bits when it is run apart.
+Choice table_choice(const fsa_plan_s* pl, const Step& s);
 Choice step_choice(const fsa_plan_s* pl, const Step& s);
+// One evaluation with the choices in force; events: fsa_apply_events' (may be null).
+hipError_t apply_plan(const fsa_plan_s* pl, const void* rho, void* phi, void* ws, hipStream_t st,
+                      hipEvent_t const* events);
 // (pass kind, transform length) of pass k of a plan.
 void pass_of(const fsa_plan_s* pl, int k, Pass* pass, int* len);
 // Transforms (rows, lines or pencils) one launch of a step runs.
@@ -281,8 +295,10 @@ int n_passes(const fsa_plan_s* pl);
 
 namespace tune {
 // Slabs of the schedule for the plan's (precision, grid); 1 unless tuned.
-int get_slabs(const fsa_plan_s* pl);
-void set_slabs(const fsa_plan_s* pl, int slabs, double us);
+// one_launch: whether passes B, C and D ran faster as one launch (1) or apart (0)
+// when the grid was tuned; -1 where that was not timed.
+int get_slabs(const fsa_plan_s* pl, int* one_launch = nullptr);
+void set_slabs(const fsa_plan_s* pl, int slabs, double us, int one_launch = -1);
 }  // namespace tune
 
 }  // namespace fsa

@@ -50,6 +50,7 @@ using GridKey = std::tuple<int, int64_t, int64_t, int64_t>;  // precision, N0, N
 struct SlabEntry {
     int slabs = 1;
     double us = 0.0;
+    int one = -1;  // passes B, C, D in one launch: 1, apart: 0, not timed: -1
 };
 
 std::mutex g_mu;
@@ -164,6 +165,7 @@ struct Parsed {
         double len = -1, var = -1, occ = -1, us = 0;
         double cls = -1;
         double slabs = -1;
+        double one = -1;
         std::vector<double> grid;
     };
     std::vector<Row> rows;   // "entries"
@@ -197,6 +199,7 @@ bool parse_row(Reader& r, Parsed::Row& row) {
             else if (k == "us") row.us = v;
             else if (k == "class") row.cls = v;
             else if (k == "slabs") row.slabs = v;
+            else if (k == "one_launch" && v >= 0.0) row.one = v;
             else return false;
         }
     } while (r.eat(','));
@@ -269,12 +272,13 @@ fsa_status load_file(const char* path) {
     for (const auto& row : p.sched) {
         const int prec = row.prec == "f32" ? FSA_F32 : row.prec == "f64" ? FSA_F64 : -1;
         bool ok = prec >= 0 && row.grid.size() == 3 && small_int(row.slabs) && row.slabs >= 1 &&
-                  row.slabs <= fsa::kMaxSlabs;
+                  row.slabs <= fsa::kMaxSlabs &&
+                  (row.one == -1 || row.one == 0 || (row.one == 1 && row.slabs == 1));
         for (double g : row.grid) ok = ok && small_int(g) && fsa::grid_length_supported((int64_t)g);
         if (!ok)
             return fail(FSA_EINVAL, "fsa_tune_load: invalid schedule entry (" + row.prec + ")");
         fresh_slabs[GridKey(prec, (int64_t)row.grid[0], (int64_t)row.grid[1],
-                            (int64_t)row.grid[2])] = SlabEntry{(int)row.slabs, row.us};
+                            (int64_t)row.grid[2])] = SlabEntry{(int)row.slabs, row.us, (int)row.one};
     }
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -311,7 +315,7 @@ int size_class(long lines) {
 namespace {
 // The entry of the nearest class among the entries of (prec, key_pass, len);
 // false if there is none.  Caller holds g_mu.
-bool nearest(int prec, int key_pass, int len, int cls, Choice* out) {
+bool nearest(int prec, int key_pass, int len, int cls, TuneEntry* out) {
     // entries of (prec, pass, len) are adjacent in the map, ordered by class
     auto lo = g_table.lower_bound(Key(prec, key_pass, len, 0));
     int dist = 1 << 30;
@@ -322,7 +326,7 @@ bool nearest(int prec, int key_pass, int len, int cls, Choice* out) {
         const int d = std::abs(std::get<3>(it->first) - cls);
         if (d < dist) {
             dist = d;
-            *out = it->second.ch;
+            *out = it->second;
         }
     }
     return dist != (1 << 30);
@@ -370,16 +374,21 @@ int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
     return 0;
 }
 
-Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched) {
+Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched, From* from) {
     load_env_once();
     const int cls = size_class(lines);
     std::lock_guard<std::mutex> lk(g_mu);
-    Choice best;
+    TuneEntry best;
+    From src = From::kUntuned;
     // a batched launch prefers the batched entries, then the single ones
-    if (batched && nearest((int)prec, (int)pass | FSA_PASS_BATCHED, len, cls, &best)) return best;
-    if (!nearest((int)prec, (int)pass, len, cls, &best))
-        best.var = default_variant(prec, pass, len, lines);
-    return best;
+    if (batched && nearest((int)prec, (int)pass | FSA_PASS_BATCHED, len, cls, &best))
+        src = From::kBatched;
+    else if (nearest((int)prec, (int)pass, len, cls, &best))
+        src = best.us > 0.0 ? From::kMeasured : From::kByHand;
+    else
+        best.ch.var = default_variant(prec, pass, len, lines);
+    if (from) *from = src;
+    return best.ch;
 }
 
 void set(fsa_precision prec, Pass pass, int len, long lines, Choice c, double us, bool batched) {
@@ -393,19 +402,23 @@ void set(fsa_precision prec, Pass pass, int len, long lines, Choice c, double us
 
 uint64_t generation() { return g_generation.load(); }
 
-int get_slabs(const fsa_plan_s* pl) {
+int get_slabs(const fsa_plan_s* pl, int* one_launch) {
+    if (one_launch) *one_launch = -1;
     if (pl->d != 3) return 1;
     load_env_once();
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_slabs.find(GridKey((int)pl->prec, pl->N[0], pl->N[1], pl->N[2]));
-    return it == g_slabs.end() ? 1 : it->second.slabs;
+    if (it == g_slabs.end()) return 1;
+    if (one_launch) *one_launch = it->second.one;
+    return it->second.slabs;
 }
 
-void set_slabs(const fsa_plan_s* pl, int slabs, double us) {
+void set_slabs(const fsa_plan_s* pl, int slabs, double us, int one_launch) {
     if (pl->d != 3) return;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        g_slabs[GridKey((int)pl->prec, pl->N[0], pl->N[1], pl->N[2])] = SlabEntry{slabs, us};
+        g_slabs[GridKey((int)pl->prec, pl->N[0], pl->N[1], pl->N[2])] =
+            SlabEntry{slabs, us, one_launch};
     }
     ++g_generation;
 }
@@ -499,13 +512,15 @@ fsa_status fsa_tune_save(const char* path) {
         std::lock_guard<std::mutex> lk(g_mu);
         bool first = true;
         for (const auto& kv : g_slabs) {
-            char line[256];
+            char line[256], one[32] = "";
+            if (kv.second.one >= 0)
+                std::snprintf(one, sizeof one, ", \"one_launch\": %d", kv.second.one);
             std::snprintf(line, sizeof line,
                           "%s\n    {\"precision\": \"%s\", \"grid\": [%lld, %lld, %lld], "
-                          "\"slabs\": %d, \"us\": %.3f}",
+                          "\"slabs\": %d%s, \"us\": %.3f}",
                           first ? "" : ",", std::get<0>(kv.first) == FSA_F32 ? "f32" : "f64",
                           (long long)std::get<1>(kv.first), (long long)std::get<2>(kv.first),
-                          (long long)std::get<3>(kv.first), kv.second.slabs, kv.second.us);
+                          (long long)std::get<3>(kv.first), kv.second.slabs, one, kv.second.us);
             out += line;
             first = false;
         }
@@ -586,7 +601,7 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
         hipError_t r = hipSuccess;
         for (int i = 0; i < ns && r == hipSuccess; ++i)
             r = fsa::launch_step(pl, steps[i], rho, phi, workspace,
-                                 fsa::step_choice(pl, steps[i]), st);
+                                 fsa::table_choice(pl, steps[i]), st);
         return r;
     };
     auto nothing = [] { return hipSuccess; };
@@ -619,8 +634,6 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
             }
         return r;
     };
-    std::vector<fsa::Choice> cands_of[5];
-    std::vector<double> us_of[5];
     // one evaluation with the current choices fills every buffer with data
     if (e == hipSuccess) e = run_all(1);
     for (int k = 0; k < np && e == hipSuccess; ++k) {
@@ -645,7 +658,7 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
             hipError_t r = hipSuccess;
             for (int j = from; j < to && r == hipSuccess; ++j)
                 r = fsa::launch_step(pl, whole(j), rho, phi, workspace,
-                                     fsa::step_choice(pl, whole(j)), st);
+                                     fsa::table_choice(pl, whole(j)), st);
             return r;
         };
         std::vector<double> us;
@@ -660,8 +673,6 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
             for (size_t c = 1; c < cands.size(); ++c)
                 if (us[c] < us[b]) b = c;
             fsa::tune::set(pl->prec, pass, len, fsa::step_lines(pl, whole(k)), cands[b], us[b]);
-            cands_of[k] = cands;
-            us_of[k] = us;
         }
     }
     // schedule: slabs of bins for the middle passes (3D)
@@ -685,69 +696,35 @@ fsa_status fsa_autotune(fsa_plan pl, const void* rho, void* phi, void* workspace
             for (size_t c = 1; c < counts.size(); ++c)
                 if (us[c] < us[b]) b = c;
             fsa::tune::set_slabs(pl, counts[b], us[b] / kBack);
-            const double apart = us[b] / kBack;
-            // passes B, C and D of a small plane in one launch: it computes what
-            // one radix family of each pass computes, so the fastest choices of
-            // those families stand in the table while it is timed, and stay if it
-            // is the faster schedule
-            fsa::Choice best[5], match[5];
-            double best_us[5], match_us[5];
-            bool have = true;
-            for (int k = 1; k <= 3; ++k) {
-                size_t w = 0, f = cands_of[k].size();
-                for (size_t c = 0; c < cands_of[k].size(); ++c) {
-                    if (us_of[k][c] < us_of[k][w]) w = c;
-                    if (fsa::plane_family(k, cands_of[k][c].var) &&
-                        (f == cands_of[k].size() || us_of[k][c] < us_of[k][f]))
-                        f = c;
-                }
-                have = have && f < cands_of[k].size();
-                if (!have) break;
-                best[k] = cands_of[k][w];
-                best_us[k] = us_of[k][w];
-                match[k] = cands_of[k][f];
-                match_us[k] = us_of[k][f];
-            }
-            auto set_passes = [&](const fsa::Choice* ch, const double* t) {
-                for (int k = 1; k <= 3; ++k) {
-                    fsa::Pass pass;
-                    int len;
-                    fsa::pass_of(pl, k, &pass, &len);
-                    fsa::tune::set(pl->prec, pass, len, fsa::step_lines(pl, whole(k)), ch[k], t[k]);
-                }
-            };
+            // passes B, C and D of a small plane in one launch, in turn with that
+            // schedule (the passes' own choices stay what was fastest for them:
+            // other grids share those entries)
             fsa::Step steps[fsa::kMaxSteps];
-            int ns = 0;
-            if (have) {
-                set_passes(match, match_us);
-                fsa::tune::set_slabs(pl, 1, apart);
-                ns = fsa::schedule_plane(pl, steps);
-            }
+            const int ns = fsa::plane_steps(pl, steps);
             if (ns > 0) {
-                std::vector<double> one;
-                e = time_rounds(1, nothing,
-                                [&](int) {
+                std::vector<double> t;
+                e = time_rounds(2, nothing,
+                                [&](int c) {
                                     hipError_t r = hipSuccess;
-                                    for (int i = 0; i < kBack && r == hipSuccess; ++i)
-                                        for (int j = 0; j < ns && r == hipSuccess; ++j)
+                                    for (int i = 0; i < kBack && r == hipSuccess; ++i) {
+                                        if (c == 0) r = run_all(counts[b]);
+                                        for (int j = 0; c == 1 && j < ns && r == hipSuccess; ++j)
                                             r = fsa::launch_step(pl, steps[j], rho, phi, workspace,
-                                                                 fsa::step_choice(pl, steps[j]), st);
+                                                                 fsa::table_choice(pl, steps[j]),
+                                                                 st);
+                                    }
                                     return r;
                                 },
-                                nothing, one);
-                if (e == hipSuccess && one[0] / kBack < apart)
-                    fsa::tune::set_slabs(pl, 1, one[0] / kBack);
-                else
-                    ns = 0;
-            }
-            if (have && ns == 0) {
-                set_passes(best, best_us);
-                fsa::tune::set_slabs(pl, counts[b], apart);
+                                nothing, t);
+                if (e == hipSuccess && t[1] < t[0])
+                    fsa::tune::set_slabs(pl, 1, t[1] / kBack, 1);
+                else if (e == hipSuccess)
+                    fsa::tune::set_slabs(pl, counts[b], t[0] / kBack, 0);
             }
         }
     }
     // leave the caller's buffers holding a valid evaluation
-    if (e == hipSuccess) e = run_all(fsa::tune::get_slabs(pl));
+    if (e == hipSuccess) e = fsa::apply_plan(pl, rho, phi, workspace, st, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     for (hipEvent_t x : ev)
         if (x) (void)hipEventDestroy(x);

@@ -49,3 +49,100 @@ def make(F, N, prec):
 def test_untuned_schedule(F, N, prec, want):
     plan, rho = make(F, N, prec)
     assert kernels(plan, rho) == want
+
+
+def arch():
+    return torch.cuda.get_device_properties(0).gcnArchName
+
+
+@pytest.mark.parametrize("N,prec", [((32, 32, 32), "f64"), ((32, 64, 16), "f32")])
+def test_a_tuned_decision_is_kept(F, N, prec, tmp_path):
+    """A table that says apart runs the passes apart, one that says one launch in one,
+    whatever the untuned choice is; the results are the same bits."""
+    plan, _ = make(F, N, prec)
+    rho = torch.randn(N, dtype=F.DTYPES[prec], device="cuda")
+    out = []
+    try:
+        for one, want in ((0, 5), (1, 3)):
+            path = tmp_path / "t.json"
+            path.write_text('{"format": "fsa-tune-1", "arch": "%s", "entries": [], "schedules": '
+                            '[{"precision": "%s", "grid": [%d, %d, %d], "slabs": 1, '
+                            '"one_launch": %d, "us": 1.0}]}' % (arch(), prec, *N, one))
+            F.tune_load(str(path))
+            assert kernels(plan, rho) == want
+            out.append(plan.apply(rho).clone())
+        torch.cuda.synchronize()
+        assert torch.equal(*out)
+    finally:
+        F.tune_reset()
+
+
+@pytest.mark.parametrize("N,prec,want", [((12, 128, 8), "f64", 5), ((16, 16, 16), "f64", 3)])
+def test_autotune_keeps_the_faster_schedule(F, N, prec, want):
+    """At 12 x 128 x 8 apart is 20% faster, at 16^3 one launch is 25% faster."""
+    plan, rho = make(F, N, prec)
+    try:
+        plan.autotune(torch.randn_like(rho), reps=9)
+        assert kernels(plan, rho) == want
+    finally:
+        F.tune_reset()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_one_launch_beside_other_choices(F, prec, tmp_path):
+    """A grid tuned to one launch keeps it where the entries of its passes, faster
+    apart, are of another radix family: fsa_apply, the passes apart and a batch (alone
+    or with a problem that follows those entries) give the same bits."""
+    N, M = (64, 32, 16), (64, 64, 16)
+    plan, _ = make(F, N, prec)
+    other, _ = make(F, M, prec)
+    rho = torch.randn(N, dtype=F.DTYPES[prec], device="cuda")
+    rho2 = torch.randn(M, dtype=F.DTYPES[prec], device="cuda")
+    base = plan.apply(rho).clone()
+    rows = ", ".join('{"precision": "%s", "pass": "%s", "length": 128, "class": %d, "variant": '
+                     '1, "occupancy": 0, "us": 5.0}' % (prec, p, c)
+                     for p in ("conv", "fwd_t", "inv_t") for c in range(8, 14))
+    path = tmp_path / "t.json"
+    path.write_text('{"format": "fsa-tune-1", "arch": "%s", "entries": [%s], "schedules": '
+                    '[{"precision": "%s", "grid": [%d, %d, %d], "slabs": 1, "one_launch": 1, '
+                    '"us": 1.0}]}' % (arch(), rows, prec, *N))
+    try:
+        F.tune_load(str(path))
+        assert kernels(plan, rho) == 3 and kernels(other, rho2) == 5
+        one = plan.apply(rho).clone()
+        two = other.apply(rho2).clone()
+        apart = plan.apply_events(rho, torch.empty_like(rho), [None] * (2 * len(plan.launches())))
+        (alone,) = F.apply_batched([plan], [rho])
+        both = F.apply_batched([plan, other], [rho, rho2])
+        torch.cuda.synchronize()
+        for x in (one, apart, alone, both[0]):
+            assert torch.equal(x, base)
+        assert torch.equal(both[1], two)
+        # set by hand, the other family is what runs
+        F.tune_set(prec, "conv", 128, 1, 0, 2 * N[1] * (N[2] + 1))
+        assert kernels(plan, rho) == 5
+    finally:
+        F.tune_reset()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_autotune_leaves_the_passes_their_fastest(F, prec, tmp_path):
+    """The entries of B, C and D name what was fastest for each pass, also where the
+    grid was tuned to one launch, and the tuned batch equals the tuned solo run."""
+    import json
+    N = (32, 32, 64)
+    plan, _ = make(F, N, prec)
+    rho = torch.randn(N, dtype=F.DTYPES[prec], device="cuda")
+    try:
+        plan.autotune(rho, reps=5)
+        path = tmp_path / "t.json"
+        F.tune_save(str(path))
+        doc = json.loads(path.read_text())
+        assert [r.get("one_launch") for r in doc["schedules"]] == [1]
+        assert {e["pass"] for e in doc["entries"]} == {"r2c", "fwd_t", "conv", "inv_t", "c2r"}
+        a = plan.apply(rho).clone()
+        (b,) = F.apply_batched([plan], [rho])
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
+    finally:
+        F.tune_reset()
