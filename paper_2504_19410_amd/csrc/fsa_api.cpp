@@ -400,15 +400,16 @@ bool runs_plane(const fsa_plan_s* pl) {
     int one = -1;
     if (!plane_fits(pl) || tune::get_slabs(pl, &one) != 1 || one == 0) return false;
     const int H = (int)pl->H;
-    // a variant that the launch does not compute: set by hand, it is wanted; tuned,
-    // it is the faster one apart, unless the grid itself was tuned to one launch
+    // a variant set by hand that the launch does not compute is wanted; tuned ones,
+    // of whichever grid's size class is nearest, were timed against their pass's
+    // other variants, not against the one launch
     for (int k = 1; k <= 3; ++k) {
         Pass pass;
         int len;
         pass_of(pl, k, &pass, &len);
         tune::From from;
         const Choice c = tune::get(pl->prec, pass, len, step_lines(pl, Step{k, 0, H}), false, &from);
-        if (!plane_family(k, c.var) && (one < 0 || from == tune::From::kByHand)) return false;
+        if (from == tune::From::kByHand && !plane_family(k, c.var)) return false;
     }
     if (one == 1) return true;
     const int P0 = (int)(2 * pl->N[0]), P1 = (int)(2 * pl->N[1]);

@@ -1,6 +1,7 @@
 """Which schedule a small 3D grid takes: the kernels one fsa_apply enqueues, counted in
 a captured graph (3 with passes B, C and D in one launch, 5 apart)."""
 import ctypes
+import os
 
 import pytest
 import torch
@@ -142,6 +143,29 @@ def test_autotune_leaves_the_passes_their_fastest(F, prec, tmp_path):
         assert {e["pass"] for e in doc["entries"]} == {"r2c", "fwd_t", "conv", "inv_t", "c2r"}
         a = plan.apply(rho).clone()
         (b,) = F.apply_batched([plan], [rho])
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
+    finally:
+        F.tune_reset()
+
+
+SHIPPED = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                       "paper_2504_19410_amd", "tune", "gfx950.json")
+
+
+@pytest.mark.parametrize("N,prec", [((64, 32, 256), "f64"), ((64, 16, 32), "f64"),
+                                    ((128, 16, 16), "f32"), ((16, 128, 64), "f32")])
+def test_entries_of_other_grids_do_not_decide(F, N, prec):
+    """The shipped table names the other radix family for passes of larger grids, whose
+    size class is the nearest one: such grids run in one launch all the same, with the
+    bits that the passes give apart."""
+    plan, rho = make(F, N, prec)
+    rho.normal_()
+    try:
+        F.tune_load(SHIPPED)
+        assert kernels(plan, rho) == 3
+        a = plan.apply(rho).clone()
+        b = plan.apply_events(rho, torch.empty_like(rho), [None] * (2 * len(plan.launches())))
         torch.cuda.synchronize()
         assert torch.equal(a, b)
     finally:
