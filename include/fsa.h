@@ -351,8 +351,8 @@ fsa_status fsa_tune_get(int precision, int pass, int length, int64_t lines, int*
  * N: the three grid lengths.  fsa_autotune times 1, 2, 4, 8, 16 slabs after
  * tuning the passes, and on small planes B, C and D in one launch, and keeps
  * which was faster with the slabs (in the file: "one_launch", 0 or 1; a count
- * set by hand leaves that to the library).  `us` (may be NULL) receives the measured evaluation
- * time of the chosen schedule (0 if set by hand or untuned). */
+ * set by hand leaves that to the library).  `us` (may be NULL) receives the
+ * measured evaluation time of the chosen schedule (0 if set by hand or untuned). */
 fsa_status fsa_tune_set_slabs(int precision, const int64_t* N, int slabs);
 fsa_status fsa_tune_get_slabs(int precision, const int64_t* N, int* slabs, double* us);
 /* Bit mask of the variants that exist at (precision, pass, length). */
@@ -360,7 +360,9 @@ fsa_status fsa_tune_variants(int precision, int pass, int length, int* mask);
 /* Writes the table as JSON (format "fsa-tune-1", tagged with the device's
  * architecture name) / merges a saved table into the current one.  Loading
  * rejects, as a whole, a file that is malformed, was tuned on another
- * architecture or names a variant that does not exist (FSA_EINVAL). */
+ * architecture or names a variant that does not exist (FSA_EINVAL).  A file
+ * says which meaning of the variant numbers it was saved under ("revision");
+ * one that does not is read with the first. */
 fsa_status fsa_tune_save(const char* path);
 fsa_status fsa_tune_load(const char* path);
 /* Forgets every entry (all passes back to their untuned choice). */

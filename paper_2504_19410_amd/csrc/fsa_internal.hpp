@@ -56,6 +56,12 @@ inline bool grid_length_supported(int64_t n) {
            fft_length_supported(2 * n);
 }
 
+// Whether the fused pass's variant 0 at length P takes one team of two waves a
+// workgroup and variant 2 two (Conv::SOLO); elsewhere 0 takes more teams than 2.
+constexpr bool conv_solo(bool f32, int P) {
+    return make_fft_plan(P).T == 128 && (f32 || P == 2048);
+}
+
 // Forget cached batch graphs that use a plan (fsa_batch.cpp).
 void batch_forget_plan(uint64_t plan_id);
 

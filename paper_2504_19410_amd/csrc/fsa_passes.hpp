@@ -651,6 +651,7 @@ struct Conv {
     // 3 * 2^a keep two (768: 376 against 380 us at 384 x 192 x 192, 260 against 266 at
     // 384 x 384 x 64; 1536: 99 against 114 at 768 x 96 x 48).
     static constexpr bool SOLO = T == 128 && (sizeof(R) == 4 || P == 2048);
+    static_assert(ALT != 0 || SOLO == conv_solo(sizeof(R) == 4, P), "the tables' reading of 0, 2");
     static constexpr int TPW = cmax(1, (SOLO != (VAR == 2) ? 128 : 256) / T);
     static constexpr int THREADS = TPW * T;
     static constexpr int LDS = TPW * Ff::SCR;

@@ -158,8 +158,13 @@ struct Reader {
     }
 };
 
+// Variants 0 and 2 of the fused pass's two-wave teams changed places (conv_solo): a
+// file of revision 1, or without one, means them the other way round.
+constexpr int kRevision = 2;
+
 struct Parsed {
     std::string format, arch;
+    double revision = 1;
     struct Row {
         std::string prec, pass;
         double len = -1, var = -1, occ = -1, us = 0;
@@ -217,6 +222,8 @@ bool parse(const std::string& text, Parsed& out) {
             std::string v;
             if (!r.str(v)) return false;
             (k == "format" ? out.format : out.arch) = v;
+        } else if (k == "revision") {
+            if (!r.num(out.revision)) return false;
         } else if (k == "entries" || k == "schedules") {
             auto& dst = k == "entries" ? out.rows : out.sched;
             if (!r.eat('[')) return false;
@@ -249,6 +256,8 @@ fsa_status load_file(const char* path) {
     if (!parse(text, p)) return fail(FSA_EINVAL, std::string("fsa_tune_load: malformed ") + path);
     if (p.format != "fsa-tune-1")
         return fail(FSA_EINVAL, "fsa_tune_load: unknown format '" + p.format + "'");
+    if (p.revision != 1 && p.revision != kRevision)
+        return fail(FSA_EINVAL, std::string("fsa_tune_load: unknown revision in ") + path);
     const std::string arch = device_arch();
     if (!arch.empty() && p.arch != arch)
         return fail(FSA_EINVAL, "fsa_tune_load: table was tuned on '" + p.arch +
@@ -260,12 +269,16 @@ fsa_status load_file(const char* path) {
         const int pass = pass_from_name(row.pass);
         const bool ints = small_int(row.len) && small_int(row.var) && small_int(row.occ) &&
                           small_int(row.cls) && row.cls <= 62;
-        const int len = ints ? (int)row.len : -1, var = ints ? (int)row.var : -1;
+        const int len = ints ? (int)row.len : -1;
+        int var = ints ? (int)row.var : -1;
         const int occ = ints ? (int)row.occ : -1;
         if (prec < 0 || pass < 0 || !ints || !length_ok(pass, len) ||
             !variant_ok((fsa_precision)prec, pass, len, var))
             return fail(FSA_EINVAL, "fsa_tune_load: invalid entry (" + row.prec + ", " +
                                         row.pass + ", " + std::to_string(len) + ")");
+        if (p.revision == 1 && (pass & ~FSA_PASS_BATCHED) == FSA_PASS_CONV &&
+            (var == 0 || var == 2) && fsa::conv_solo(prec == FSA_F32, len))
+            var = 2 - var;
         fresh[Key(prec, pass, len, (int)row.cls)] = TuneEntry{fsa::Choice{var, occ}, row.us};
     }
     std::map<GridKey, SlabEntry> fresh_slabs;
@@ -489,7 +502,8 @@ fsa_status fsa_tune_reset(void) {
 fsa_status fsa_tune_save(const char* path) {
     if (!path) return fail(FSA_EINVAL, "fsa_tune_save: null path");
     load_env_once();
-    std::string out = "{\n  \"format\": \"fsa-tune-1\",\n  \"arch\": \"" + device_arch() +
+    std::string out = "{\n  \"format\": \"fsa-tune-1\",\n  \"revision\": " +
+                      std::to_string(kRevision) + ",\n  \"arch\": \"" + device_arch() +
                       "\",\n  \"entries\": [";
     {
         std::lock_guard<std::mutex> lk(g_mu);
