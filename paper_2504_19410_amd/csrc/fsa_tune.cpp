@@ -367,9 +367,17 @@ bool nearest(int prec, int key_pass, int len, int cls, TuneEntry* out) {
 // pass C 128 19.5 / 19.8 at 64 x 64 x 512 and 5.0 / 6.1 at 64^2).
 int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
     const bool f32 = prec == FSA_F32;
+    // at most one workgroup per CU of variant 3 of the real passes
+    auto own_cu = [&] {
+        if (lines >= 1 << 24) return false;
+        const JobR2c a{nullptr, nullptr, 1, (int)lines};
+        const JobC2r e{nullptr, nullptr, 1, (int)lines, nullptr, 0.0};
+        const void* job = pass == Pass::R2C ? (const void*)&a : (const void*)&e;
+        return Launch<double>::items(pass, len, job, Choice{3, 0}) <= device_cus();
+    };
     switch (pass) {
     case Pass::R2C:
-        if (!f32 && len == 768 && lines <= 1024) return 3;
+        if (!f32 && len == 768 && own_cu()) return 3;
         return !f32 && len == 1024;  // 31.3 / 20.8 (1024^2)
     case Pass::FWD_T:
         if (f32 && len == 768 && lines >= 1 << 15) return 3;
@@ -381,7 +389,7 @@ int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
                || (f32 ? len == 2048                  // 104 / 96 (128 x 1024 x 64)
                        : len == 1024);                // 261 / 195 (512 x 512 x 64)
     case Pass::C2R:
-        if (!f32 && len == 768 && lines <= 1024) return 3;
+        if (!f32 && len == 768 && own_cu()) return 3;
         return !f32 && (len == 1024 || len == 2048);  // 16.0 / 10.2 (1024^2), 59.5 / 40.6
     }
     return 0;
