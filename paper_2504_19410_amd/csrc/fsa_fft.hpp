@@ -22,7 +22,9 @@
 // Every per-thread phase is __host__ __device__ so that the index logic can
 // be emulated thread by thread on the CPU (tests/host).  Twiddles come from
 // tables built in FP64 (rounded to the transform's precision once): the plain
-// table tw[m] = exp(-2 pi i m / P), or the staged tables (StagedTw).
+// table tw[m] = exp(-2 pi i m / P), or the staged tables (staged_index), which the
+// kernels read.  The plain form of the stages (compute, load_tw) is the host tests'
+// reference for the staged one.
 #pragma once
 
 #if defined(__HIPCC__)
@@ -434,8 +436,9 @@ constexpr bool fft_alt_distinct(int P) {
 // were bound by those loads (the vector L1 takes one line a clock): at 512 x
 // 512 x 64 passes B, C, D of length 1024 went from 270, 516 and 296 us to 173,
 // 414 and 262, pass E of 2048^2 from 78 to 60 us.
-// A length's tables follow each other: the plain one, then, P entries each,
-// family 0 forward and inverse and family 1 forward and inverse.
+// A length's tables follow each other: the plain one (read for the real passes'
+// pre- and post-processing and by the host tests), then, P entries each, family 0
+// forward and inverse and family 1 forward and inverse.
 constexpr int kTwTables = 5;
 constexpr int staged_table(int alt, bool inv) { return 1 + 2 * alt + (inv ? 1 : 0); }
 
