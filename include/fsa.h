@@ -227,7 +227,7 @@ fsa_status fsa_batch_workspace_bytes(int n, const fsa_plan* plans, size_t* bytes
  * and precision) as one hipGraph of persistent launches: for each pass, in
  * dependency order, and each transform length that pass uses, ONE launch
  * walks the work items (problem, tile or pencil) of every problem that
- * shares the length.  The graph is captured on first use of a batch
+ * shares the length (two where their radix families differ).  The graph is captured on first use of a batch
  * signature and replayed afterwards.  A launch takes the tuning table's
  * choice for its total number of transforms (fsa_autotune_batched tunes
  * those); under the same launch choices each problem's result is bitwise
@@ -245,7 +245,7 @@ fsa_status fsa_apply_batched(int n, const fsa_plan* plans, const void* const* rh
                              void* stream);
 
 /* Number of persistent launches in the graph captured for this batch
- * signature (one per pass and transform length); FSA_ESTATE if the batch
+ * signature (one per pass, transform length and radix family); FSA_ESTATE if the batch
  * has not been run yet.  For tests and tools. */
 fsa_status fsa_batch_launches(int n, const fsa_plan* plans, const void* const* rho,
                               void* const* phi, void* workspace, int* launches);
@@ -296,9 +296,10 @@ typedef enum {
  * and its persistent grid may use `occupancy` resident workgroups per CU
  * (0 = as many as fit).  The library keeps one process-wide table of
  * choices; untuned entries use variant 0 at full occupancy, or the variant that
- * is the faster one on every grid timed at that (precision, pass, length)
- * (fsa_tune_get reports it; by the lines only between variants that
- * compute bitwise the same).  fsa_apply, fsa_apply_batched and the
+ * was measured faster at that (precision, pass, length) for launches of about
+ * as many lines (fsa_tune_get reports it).  The radix family of that choice
+ * follows the lines of each whole problem, so that slabs and batches compute
+ * bitwise what the problem computes alone in one piece.  fsa_apply, fsa_apply_batched and the
  * server read the table when they launch.  All
  * variants compute the same transform; results differ only by rounding.
  * On first use the table is loaded from the JSON file named by the

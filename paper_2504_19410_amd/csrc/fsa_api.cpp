@@ -440,7 +440,8 @@ Choice table_choice(const fsa_plan_s* pl, const Step& s) {
     Pass pass;
     int len;
     pass_of(pl, s.k, &pass, &len);
-    return tune::get(pl->prec, pass, len, step_lines(pl, s));
+    return tune::get(pl->prec, pass, len, step_lines(pl, s), false, nullptr,
+                     step_lines(pl, Step{s.k, 0, (int)pl->H}));
 }
 
 Choice step_choice(const fsa_plan_s* pl, const Step& s) {

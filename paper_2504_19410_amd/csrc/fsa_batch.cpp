@@ -4,7 +4,8 @@
 // precisions) runs as a hipGraph of persistent launches: for every pass
 // (A, B, C, D, E, in dependency order) and every transform length used by
 // that pass, ONE launch walks the work items of all problems that share the
-// length, through a device table of per-problem jobs.  Kernel boundaries
+// length (two where the problems' radix families differ, split_families), through
+// a device table of per-problem jobs.  Kernel boundaries
 // order the passes, so no cross-workgroup synchronisation (and no multi-XCD
 // L2 write-back/invalidate traffic) is needed inside a launch.  Each item
 // runs exactly the code of the single-problem path, so a batched result is
@@ -66,7 +67,7 @@ struct Group {
     // other bits)
     std::vector<long> job_lines;
     std::vector<bool> plane;
-    bool family = false;  // all jobs do, and the table's choice is outside it
+    bool family = false;  // they do, and the table's choice is outside it
 };
 
 struct Entry {
@@ -165,26 +166,27 @@ hipError_t launch_group(const Group& g, const char* tables, hipStream_t st) {
 
 using Groups = std::map<std::tuple<int, int, int, int>, Group>;
 
-// The table's choice for a group.
+// The table's choice for a group, whose jobs are of one family (split_families).
 fsa::Choice group_choice(const Group& g) {
-    return g.family ? fsa::Choice{} : fsa::tune::get(g.prec, g.pass, g.len, g.lines, true);
+    return g.family ? fsa::Choice{}
+                    : fsa::tune::get(g.prec, g.pass, g.len, g.lines, true, nullptr,
+                                     g.job_lines[0]);
 }
 
-// Where single-evaluation entries give a group a choice outside the radix family of
-// the one launch of B, C and D, the jobs of plans that run that launch get a group of
-// their own on variant 0, and each problem computes what it computes alone.
-void split_planes(Groups& groups) {
+// Each problem computes what it computes alone: where its untuned choice is another
+// radix family than a neighbour's, or where single-evaluation entries give the group a
+// choice outside the family of the one launch of B, C and D that it runs, such jobs
+// get a group (in the latter case on variant 0) of their own.
+void split_families(Groups& groups) {
     Groups apart;
     for (auto it = groups.begin(); it != groups.end();) {
         Group& g = it->second;
         const auto key = it->first;
         fsa::tune::From from;
         const fsa::Choice c = fsa::tune::get(g.prec, g.pass, g.len, g.lines, true, &from);
-        if (from == fsa::tune::From::kBatched || fsa::plane_family((int)g.pass, c.var) ||
-            std::find(g.plane.begin(), g.plane.end(), true) == g.plane.end()) {
-            ++it;
-            continue;
-        }
+        const bool untuned = from == fsa::tune::From::kUntuned;
+        const bool outside = !untuned && from != fsa::tune::From::kBatched &&
+                             !fsa::plane_family((int)g.pass, c.var);
         Group part[2];
         for (int f = 0; f < 2; ++f) {
             part[f].pass = g.pass;
@@ -193,10 +195,13 @@ void split_planes(Groups& groups) {
             part[f].tw = g.tw;
             part[f].tw2 = g.tw2;
             part[f].job_size = g.job_size;
-            part[f].family = f == 1;
+            part[f].family = outside && f == 1;
         }
         for (int i = 0; i < g.n; ++i) {
-            Group& p = part[g.plane[i] ? 1 : 0];
+            const int f = untuned ? fsa::tune::default_family(g.prec, g.pass, g.len,
+                                                              g.job_lines[i])
+                                  : outside && g.plane[i];
+            Group& p = part[f];
             const unsigned char* job = g.jobs.data() + (size_t)i * g.job_size;
             p.jobs.insert(p.jobs.end(), job, job + g.job_size);
             p.job_lines.push_back(g.job_lines[i]);
@@ -211,7 +216,7 @@ void split_planes(Groups& groups) {
                                               std::get<2>(key), f),
                               std::move(part[f]));
     }
-    groups.merge(apart);
+    groups.swap(apart);
 }
 
 // Sorts the problems' jobs into (pass, length, precision) groups; the
@@ -260,7 +265,7 @@ fsa_status make_groups(int n, const fsa_plan* plans, const void* const* rho, voi
             return FSA_EUNSUPPORTED;
         }
     }
-    split_planes(groups);
+    split_families(groups);
     return FSA_OK;
 }
 

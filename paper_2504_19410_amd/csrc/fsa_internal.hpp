@@ -247,10 +247,13 @@ namespace tune {
 int size_class(long lines);
 // `batched`: the entries of the batched persistent launches (a batched get
 // falls back to the single-evaluation entries where it has none).  from: where the
-// choice comes from.
+// choice comes from.  problem_lines: the lines of the whole problem that the launch
+// runs a slab of, or of each problem of a batch (0: lines), for the untuned family.
 enum class From { kUntuned, kByHand, kMeasured, kBatched };
 Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched = false,
-           From* from = nullptr);
+           From* from = nullptr, long problem_lines = 0);
+// The radix family (variant 0's or 1's) of an untuned pass of a problem.
+int default_family(fsa_precision prec, Pass pass, int len, long lines);
 void set(fsa_precision prec, Pass pass, int len, long lines, Choice c, double us,
          bool batched = false);
 // Bumped on every change; batch graphs captured under another generation

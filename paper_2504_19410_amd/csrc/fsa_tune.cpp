@@ -346,26 +346,61 @@ bool nearest(int prec, int key_pass, int len, int cls, TuneEntry* out) {
 }
 }  // namespace
 
-// The variant of an untuned (precision, pass, length): 0, except where the
-// other radix family is faster on every grid that was timed (us, variant 0 /
-// variant 1).  The lines a launch runs choose between variants of one family at
-// most, so that a batch of untuned problems computes bitwise what each computes
-// alone.
-//   Teams of 8 operands per thread fill wider workgroups: in passes B and D
-// whole tiles of 1024 threads; in the real passes one FP64 row of 1024 no
-// longer spills (256 VGPRs and 324 bytes of scratch -> 212 VGPRs).
-//   At 768 the narrower team of family 1 (64 threads of 16 operands) doubles
-// the lines per tile, i.e. the bytes per row that passes B and D write and read.
-// In FP32 that is half a cache line; once X2 outgrows the Infinity Cache (from
-// 2^15 lines, 200 MB), pass B takes variant 3, the same family on whole lines:
-// 192 x 384 x 128 231 / 230 us, 192 x 384 x 192 360 / 349, 256 x 384 x 256 668 /
-// 580 (variant 1 / 3), but 128 x 384 x 128 146 / 154.  The real passes of 768 in
-// FP64 take variant 3 while every workgroup (4 rows) has a CU of its own: 1024 x 768
-// 43.8 / 36.0 us, 32 x 32 x 768 46.5 / 40.6, but 192 x 64 x 768 466 / 477 (variant 0 / 3).
-//   Close calls stay with variant 0: what family 1 gains on large grids it loses
-// on small ones (FP32 pass E 384 162 / 155 us at 384^3 but 5.8 / 7.9 at 256 x 384,
-// pass C 128 19.5 / 19.8 at 64 x 64 x 512 and 5.0 / 6.1 at 64^2).
-int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
+// The radix family of an untuned pass, by the lines of its problem: the default one
+// (0), except where the alternate one (1) is the faster (us, family 0 / 1, every pass
+// below timed in both on one build; `lines` as step_lines counts them).  Slabs and
+// batches ask with each problem's own lines, so that both compute bitwise what the
+// problem computes alone in one piece.
+//   Teams of 8 operands per thread fill wider workgroups, whole tiles of 1024
+// threads in passes B and D, which pays once a launch fills the device several times
+// over; one FP64 row of 1024 no longer spills (256 VGPRs and 580 bytes of scratch ->
+// 212 VGPRs).  At 768 the narrower team of family 1 (64 threads of 16 operands)
+// doubles the lines per tile, i.e. the bytes per row that passes B and D write and
+// read, and loses where a launch is less than a tile per CU or two.
+//   Close calls stay with family 0 (FP32 pass E 384 162 / 155 at 384^3 but 5.8 / 7.9 at
+// 256 x 384, pass C 128 19.5 / 19.8 at 64 x 64 x 512 and 5.0 / 6.1 at 64^2).
+int default_family(fsa_precision prec, Pass pass, int len, long lines) {
+    const bool f32 = prec == FSA_F32;
+    switch (pass) {
+    case Pass::R2C:
+        return !f32 && len == 1024;  // 33.5 / 9.7 (256 rows), 86 / 32 (4096), 217 / 80 (12288)
+    case Pass::FWD_T:
+        // FP32 6.4 / 7.5 (72 lines), 8.4 / 8.9 (528), 8.5 / 8.2 (1056), 15.2 / 14.0 (4160),
+        // 665 / 412 (147840); FP64 8.0 / 8.4 (72), 9.6 / 9.4 (272), 183 / 165 (37056)
+        if (len == 768) return lines >= (f32 ? 1024 : 256);
+        // 8.2 / 10.1 (272), 17.3 / 20.6 (4160), 36.3 / 37.7 (12352), 51.1 / 46.5 (16640),
+        // 112 / 94 (33280)
+        if (f32 && len == 1024) return lines >= 1 << 14;
+        // 10.4 / 11.4 (272), 30.8 / 31.5 (4160), 52.0 / 48.5 (8224)
+        return f32 && len == 2048 && lines >= 1 << 13;
+    case Pass::CONV: return 0;
+    case Pass::INV_T:
+        // FP32 6.3 / 7.6 (72), 7.7 / 8.0 (528), 10.6 / 8.4 (1056), 482 / 326 (147840);
+        // FP64 7.9 / 8.1 (72), 8.8 / 8.5 (272), 188 / 161 (37056)
+        if (len == 768) return lines >= (f32 ? 1024 : 256);
+        // 10.2 / 11.0 (272), 22.8 / 23.1 (2080), 39.0 / 37.4 (4160), 72.8 / 66.1 (8224)
+        if (f32) return len == 2048 && lines >= 1 << 12;
+        // 11.6 / 10.8 (72), 13.0 / 12.8 (1056), 22.9 / 23.1 (2080), 33.6 / 35.7 (4160),
+        // 57.7 / 60.8 (9312), 101 / 85 (12352), 261 / 191 (33280)
+        return len == 1024 && (lines < 1 << 11 || lines >= 3 << 12);
+    case Pass::C2R:
+        // 1024: 13.4 / 8.0 (256 rows), 14.1 / 10.0 (1024), 25.5 / 23.2 (2304), 94 / 85
+        // (9216), though 15.0 / 17.4 at 2048 and 28.0 / 32.6 at 4096, where family 0 ends
+        // on a full round of workgroups; 2048: 12.7 / 9.8 (256), 116 / 89 (4096)
+        return !f32 && (len == 1024 || len == 2048);
+    }
+    return 0;
+}
+
+// The variant of that family for a launch of `lines` lines: 0 or 1, or variant 3 of
+// the same family, which computes the same bits.
+//   Pass B, FP32 at 768: family 1 writes half a cache line a row; once X2 outgrows the
+// Infinity Cache (from 2^15 lines, 200 MB), variant 3 writes whole ones (variant 1 / 3:
+// 192 x 384 x 192 82.7 / 75.3, 384^3 412 / 313, but 128 x 384 x 128 35.5 / 36.8).
+//   The real passes, FP64 at 768: variant 3 while every workgroup (4 rows) has a CU
+// of its own (passes A and E, variant 0 / 3: 1024 x 768 18.6 / 14.7 and 12.4 / 8.8, 32 x
+// 48 x 768 19.8 / 21.3 and 14.1 / 14.1, 192 x 64 x 768 86 / 81 and 84 / 92).
+int default_variant(fsa_precision prec, Pass pass, int len, long lines, int family) {
     const bool f32 = prec == FSA_F32;
     // at most one workgroup per CU of variant 3 of the real passes
     auto own_cu = [&] {
@@ -375,27 +410,13 @@ int default_variant(fsa_precision prec, Pass pass, int len, long lines) {
         const void* job = pass == Pass::R2C ? (const void*)&a : (const void*)&e;
         return Launch<double>::items(pass, len, job, Choice{3, 0}) <= device_cus();
     };
-    switch (pass) {
-    case Pass::R2C:
-        if (!f32 && len == 768 && own_cu()) return 3;
-        return !f32 && len == 1024;  // 31.3 / 20.8 (1024^2)
-    case Pass::FWD_T:
-        if (f32 && len == 768 && lines >= 1 << 15) return 3;
-        return len == 768                             // FP32 763 / 398, FP64 402 / 322 (384^3)
-               || (f32 && (len == 1024 || len == 2048));  // 130 / 101 (512 x 512 x 64), 85 / 70
-    case Pass::CONV: return 0;
-    case Pass::INV_T:
-        return len == 768                             // FP32 488 / 336, FP64 354 / 292 (384^3)
-               || (f32 ? len == 2048                  // 104 / 96 (128 x 1024 x 64)
-                       : len == 1024);                // 261 / 195 (512 x 512 x 64)
-    case Pass::C2R:
-        if (!f32 && len == 768 && own_cu()) return 3;
-        return !f32 && (len == 1024 || len == 2048);  // 16.0 / 10.2 (1024^2), 59.5 / 40.6
-    }
-    return 0;
+    if (pass == Pass::FWD_T && f32 && len == 768 && family == 1 && lines >= 1 << 15) return 3;
+    if ((pass == Pass::R2C || pass == Pass::C2R) && !f32 && len == 768 && own_cu()) return 3;
+    return family;
 }
 
-Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched, From* from) {
+Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched, From* from,
+           long problem_lines) {
     load_env_once();
     const int cls = size_class(lines);
     std::lock_guard<std::mutex> lk(g_mu);
@@ -407,7 +428,9 @@ Choice get(fsa_precision prec, Pass pass, int len, long lines, bool batched, Fro
     else if (nearest((int)prec, (int)pass, len, cls, &best))
         src = best.us > 0.0 ? From::kMeasured : From::kByHand;
     else
-        best.ch.var = default_variant(prec, pass, len, lines);
+        best.ch.var = default_variant(
+            prec, pass, len, lines,
+            default_family(prec, pass, len, problem_lines > 0 ? problem_lines : lines));
     if (from) *from = src;
     return best.ch;
 }
