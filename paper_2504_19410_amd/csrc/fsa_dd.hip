@@ -21,7 +21,7 @@
 // stays with one line, so its addresses cost one division each.  The arithmetic
 // bounds it (a double-double addition is 20 FP64 operations, a product 10): 64^3
 // took 344 us on the whole complex spectrum with one line per workgroup of P / 4
-// threads (half a wave at P = 128), 163 us this way; its fused pass 186 us, now 76.
+// threads (half a wave at P = 128), 156 us this way; its fused pass 180 us, now 77.
 // Arrays of reals are interleaved (hi, lo) pairs; complex values are
 // (re.hi, re.lo, im.hi, im.lo).
 #include <hip/hip_runtime.h>

@@ -31,19 +31,28 @@ namespace fsa {
 
 // Shape of a launch of the double-double transforms: threads per line of length P
 // (one radix-4 butterfly each and step, where the line is short enough) and lines
-// per workgroup, of up to 256 threads.  A launch of fewer workgroups than CUs takes
-// fewer lines in each, down to one wave: its time is one workgroup's, and the waves
-// of a CU share what each of them then has alone (64 x 64 39.9 us with one line of
-// 32 threads per workgroup, 48.3 with groups of 256 threads, 36.4 with this rule;
-// 8 x 8 x 8 43.2, 46.9, 37.3; half a wave: 40.9 and 38.9).
+// per workgroup, of up to 256 threads.  A launch of fewer than four workgroups per CU
+// takes as long as its fullest CU: there the workgroups get smaller, down to one
+// wave, while that leaves fewer lines on it (64 x 64 39.9 us with one line of 32 threads
+// per workgroup, 48.3 with groups of 256 threads, 36.4 with this rule; 8 x 8 x 8 43.2,
+// 46.9, 37.3; 128 x 512 68.0, 55.7, 51.6; half a wave: 64 x 64 40.9 us; smaller groups
+// where the fullest CU has as many lines: 1024 x 256 128 us against 124).
 constexpr int kDDThreads = 256;
 constexpr int kDDMaxP = 2048;
 constexpr int dd_line_threads(int P) { return P >= 4 * kDDThreads ? kDDThreads : P / 4; }
 constexpr int dd_lines(int P, long lines, int cus) {
     const int n = dd_line_threads(P);
-    int W = kDDThreads / n;
-    while (W * n > 64 && W > 1 && (lines + W - 1) / W < cus) W /= 2;
-    return W;
+    int best = kDDThreads / n;
+    long fewest = 0;
+    for (int W = best; W >= 1; W /= 2) {
+        const long groups = (lines + W - 1) / W, on_one = (groups + cus - 1) / cus * W;
+        if (fewest == 0 || on_one < fewest) {
+            best = W;
+            fewest = on_one;
+        }
+        if (groups >= 4 * (long)cus || W * n <= 64) break;
+    }
+    return best;
 }
 
 struct dd {

@@ -1,7 +1,7 @@
 // Lines per workgroup of the double-double transforms (dd_lines), at every length,
 // over line counts and CU counts.  Prints "ok" if every launch is within the limits
-// its kernels assume and a launch that cannot give every CU a workgroup takes no
-// more than one wave's lines in each.
+// its kernels assume and no allowed shape of a launch of few workgroups leaves fewer
+// lines on the fullest CU, or as few in larger workgroups.
 #include <cstdio>
 #include <initializer_list>
 
@@ -21,9 +21,12 @@ int main() {
                 const long groups = (lines + W - 1) / W;
                 if (W < 1 || (W & (W - 1)) != 0 || W * n > kDDThreads) ++bad;
                 if (2 * W * P * 16 > 65536) ++bad;  // LDS bytes of the tile
-                if (groups < cus && W > 1 && W * n > 64) ++bad;
-                // and no fewer lines than that needs
-                if (2 * W * n <= kDDThreads && (lines + 2 * W - 1) / (2 * W) >= cus) ++bad;
+                auto on_one = [&](int w) { return ((lines + w - 1) / w + cus - 1) / cus * w; };
+                bool few = true;  // every larger shape has fewer than four groups per CU
+                for (int w = kDDThreads / n; w >= 1 && w * n >= 64; w /= 2) {
+                    if (few && (on_one(w) < on_one(W) || (on_one(w) == on_one(W) && w > W))) ++bad;
+                    few = few && (lines + w - 1) / w < 4 * cus;
+                }
             }
         }
     std::printf(bad ? "bad %d\n" : "ok\n", bad);

@@ -16,8 +16,9 @@ TOL_DD = 1e-30
 @pytest.mark.parametrize("kind,N", [
     ("coulomb2d", (64, 64)),       # 32 row pairs and 65 lines of 128: one wave each
     ("coulomb2d", (16, 512)),      # 513 lines of 32: one wave (8 lines), partial last group
-    ("coulomb3d", (32, 32, 32)),   # 2112 lines of 64 in the fused pass: two waves
-    ("coulomb3d", (8, 64, 128)),   # 16512 lines of 16 in the fused pass: four waves
+    ("coulomb3d", (8, 32, 512)),   # 32832 lines of 16 in the fused pass: two waves
+    ("coulomb3d", (8, 64, 512)),   # 65664: four waves, 4104 lines of 128 on axis 1: two
+    ("coulomb3d", (32, 32, 32)),   # 2112 lines of 64 in the fused pass: one
 ])
 def test_parity_dd_group_sizes(kind, N):
     if not torch.cuda.is_available():
