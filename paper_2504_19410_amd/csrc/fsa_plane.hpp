@@ -62,14 +62,17 @@ struct Plane {
     // another (pass D and the inverse of C repeat them)
     static constexpr int CHAIN = RB * F1::V * F1::S + RC * F0::V * F0::S;
     // Planes whose workgroup is slower than the three launches while few of them run
-    // side by side: in FP64, long chains.  One launch / apart, us: 12 x 96 at N_2 = 8,
-    // 32, 64, 96 22.5 / 20.3, 23.9 / 21.0, 24.2 / 22.6, 29.8 / 30.6; 96 x 16 20.3 /
-    // 20.0, 21.6 / 20.0, 22.0 / 21.9, 27.7 / 31; 24 x 64 at 16, 32, 48, 64 21.3 / 20.5,
-    // 21.5 / 21.1, 27.4 / 27.5, 21.9 / 23.1.  The others gain in a stream at every N_2
-    // (64 x 32, chain 64, at N_2 = 8: 18.2 / 19.6), where five launches take 20 us at
-    // least; replayed from a graph, where that is 16, some lose at N_2 = 8 (17.9 / 16.0).
-    static constexpr bool FEW_SLOW = sizeof(R) == 8 && N0 * N1 > 1024 && CHAIN >= 120;
-    static constexpr int FEW = cmax(P0, P1) >= 192 ? 96 : 64;
+    // side by side: in FP64, long chains along long axes.  One launch / apart, us: 12 x
+    // 96 at N_2 = 8, 32, 64, 96 22.5 / 20.3, 23.9 / 21.0, 24.2 / 22.6, 29.8 / 30.6; 96 x 16
+    // 20.3 / 20.0, 21.6 / 20.0, 22.0 / 21.9, 27.7 / 31; but 24 x 64, as long a chain, at 8,
+    // 16, 32, 64 20.1 / 20.0, 21.3 / 20.5, 21.5 / 21.1, 21.9 / 23.1.  The others gain in a
+    // stream at every N_2 (64 x 32 at N_2 = 8: 18.2 / 19.6), where five launches take 20
+    // us at least; replayed from a graph, where that is 16, some lose up to N_2 = 32
+    // (64 x 32, 128 x 16, 96 x 8 FP64 at 8: 17.8 / 16.0, 18.4 / 16.2, 17.5 / 15.9): a
+    // grid's schedule in the tuning table says so ("one_launch": 0).
+    static constexpr bool FEW_SLOW =
+        sizeof(R) == 8 && N0 * N1 > 1024 && CHAIN >= 120 && cmax(P0, P1) >= 192;
+    static constexpr int FEW = 96;
 };
 
 template <typename R, int P1, int P0>

@@ -42,7 +42,7 @@ def make(F, N, prec):
     ((16, 128, 8), "f64", 3), ((32, 64, 512), "f32", 3), ((32, 64, 512), "f64", 3),
     # few FP64 planes with a long chain per thread
     ((12, 96, 8), "f64", 5), ((12, 128, 64), "f64", 5), ((96, 16, 48), "f64", 5),
-    ((24, 64, 48), "f64", 5), ((24, 64, 64), "f64", 3), ((12, 96, 96), "f64", 3), ((96, 16, 96), "f64", 3),
+    ((12, 96, 64), "f64", 5), ((24, 64, 48), "f64", 3), ((12, 96, 96), "f64", 3), ((96, 16, 96), "f64", 3),
     ((12, 96, 8), "f32", 3), ((96, 8, 8), "f64", 3),
     # past the plane's size, and an axis longer than 128
     ((48, 48, 8), "f32", 5), ((8, 192, 8), "f32", 5),
