@@ -170,8 +170,10 @@ fsa_status fsa_build_tensor(fsa_plan plan, void* stream);
 
 /* One evaluation (Execution in the paper's terms): phi = crop(IDFT(T^ .
  * DFT(pad(rho)))) through 3 (2D) or 5 (3D) kernels enqueued on `stream` (3 on
- * small 3D grids, N_0 N_1 <= 2048, whose three middle passes run as one);
- * returns without host synchronisation.
+ * small 3D grids, N_0 and N_1 <= 128 with N_0 N_1 <= 2048, whose three middle
+ * passes run as one where that is the faster schedule: untuned, or as
+ * fsa_autotune found; slabs, and variants set by hand that the one launch does
+ * not compute, keep them apart); returns without host synchronisation.
  *   rho        device input, plan precision, shape N (read only).
  *   phi        device output, plan precision, shape N; may equal rho.
  *   workspace  device scratch of at least workspace_bytes (fsa_plan_query),

@@ -44,9 +44,13 @@ CXXFLAGS = [
     # keep the compiler from forming packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # and from pairing LDS accesses (ds_read2_b64 and ds_write2_b64): a paired FP32
-    # exchange meets the banks its two halves miss one at a time, and its
-    # register quads cost registers (pass C at 192^3 65.3 -> 60.4 us, at 384^3
-    # 611 -> 568; FP64 accesses, 16 bytes wide, are never paired)
+    # exchange meets the banks its two halves miss one at a time, and its register
+    # quads cost registers (FP32 pass C at 192^3 65.3 -> 60.4 us, at 384^3 611 -> 568).
+    # The switch holds for every kernel.  It changes the resident waves or the scratch
+    # of 60: 53 gain, among them pass B in FP32 and the tensor build's exchanges of
+    # single doubles, and of the others one is an untuned choice (C2r::WAVES).  Complex
+    # doubles, 16 bytes wide, are not paired either way; builds and dipole-dipole
+    # derivatives take the same time with and without it.
     "-Xclang", "-target-feature", "-Xclang", "-load-store-opt",
     "-Wall", "-Wno-unused-function",
 ]

@@ -12,12 +12,14 @@
 // Each transform is the same team FFT, on the same radices, as the pass of its
 // own launch computes, so the results are bitwise the same.
 //
-// The line at N0 N1 <= 2048: a plane is one workgroup's work, whose arithmetic
-// grows with the plane and cannot spread over the device when the planes are
-// fewer than the CUs.  Evaluations in us, separate / in one launch: 16^3 20.3 /
-// 13.0, 32^3 FP64 20.5 / 14.3, 32 x 64 x 64 20.3 / 16.1 FP32 and 22.3 / 19.0
-// FP64, 64 x 32 x 256 34.6 / 24.0 and 38.5 / 34.3; past the line 48 x 48 x 256
-// FP32 37.2 / 38.1, 64 x 64 x 256 FP64 56.3 / 62.1, 32 x 128 x 64 FP64 31.1 / 39.3.
+// The line at N0 N1 <= 2048 (axes of at most 128, the lengths it is compiled for): a
+// plane is one workgroup's work, whose arithmetic grows with the plane and cannot
+// spread over the device when the planes are fewer than the CUs.  Evaluations in us,
+// separate / in one launch: 32^3 FP64 20.4 / 14.7, 32 x 64 x 64 20.1 / 16.3 FP32 and
+// 22.1 / 18.8 FP64, 64 x 32 x 256 32.8 / 24.2 and 35.9 / 32.9; past the line 48 x 48 x 256
+// FP32 37.2 / 38.1, 64 x 64 x 256 FP64 56.3 / 62.1, 32 x 128 x 64 FP64 31.1 / 39.3.  Longer
+// last axes only add planes: 32 x 64 x 2048 113 / 87 (FP32) and 205 / 158 (FP64).
+// Exceptions: FEW_SLOW.
 #pragma once
 
 #include "fsa_fft.hpp"
