@@ -12,9 +12,10 @@
 // slabs of bins p2 the middle passes B, C, D are run in (B, C, D of one slab
 // back to back, so the slab's spectrum can stay in the memory-side cache
 // between them), and on small planes B, C and D in one launch against that, and
-// keeps the fastest per (precision, grid).  fsa_apply, fsa_apply_batched and the server read the tables at launch time.  They can
-// be saved to and loaded from a JSON file, and are loaded on first use from
-// the file named by the environment variable FSA_TUNE_CACHE when that is set.
+// keeps the fastest per (precision, grid).  fsa_apply, fsa_apply_batched and the
+// server read the tables at launch time.  They can be saved to and loaded from a
+// JSON file, and are loaded on first use from the file named by the environment
+// variable FSA_TUNE_CACHE when that is set.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
