@@ -358,6 +358,8 @@ bool nearest(int prec, int key_pass, int len, int cls, TuneEntry* out) {
 // 212 VGPRs).  At 768 the narrower team of family 1 (64 threads of 16 operands)
 // doubles the lines per tile, i.e. the bytes per row that passes B and D write and
 // read, and loses where a launch is less than a tile per CU or two.
+//   A batch of small problems runs the family of small ones on many lines, so a bound
+// lies where the smaller side gains more than a batch loses: not for a few per cent.
 //   Close calls stay with family 0 (FP32 pass E 384 162 / 155 at 384^3 but 5.8 / 7.9 at
 // 256 x 384, pass C 128 19.5 / 19.8 at 64 x 64 x 512 and 5.0 / 6.1 at 64^2).
 int default_family(fsa_precision prec, Pass pass, int len, long lines) {
@@ -366,9 +368,9 @@ int default_family(fsa_precision prec, Pass pass, int len, long lines) {
     case Pass::R2C:
         return !f32 && len == 1024;  // 33.5 / 9.7 (256 rows), 86 / 32 (4096), 217 / 80 (12288)
     case Pass::FWD_T:
-        // FP32 6.4 / 7.5 (72 lines), 8.4 / 8.9 (528), 8.5 / 8.2 (1056), 15.2 / 14.0 (4160),
+        // FP32 6.4 / 7.5 (72 lines), 7.5 / 8.2 (272), 8.5 / 8.2 (1056), 15.2 / 14.0 (4160),
         // 665 / 412 (147840); FP64 8.0 / 8.4 (72), 9.6 / 9.4 (272), 183 / 165 (37056)
-        if (len == 768) return lines >= (f32 ? 1024 : 256);
+        if (len == 768) return lines >= 256;
         // 8.2 / 10.1 (272), 17.3 / 20.6 (4160), 36.3 / 37.7 (12352), 51.1 / 46.5 (16640),
         // 112 / 94 (33280)
         if (f32 && len == 1024) return lines >= 1 << 14;
@@ -376,14 +378,14 @@ int default_family(fsa_precision prec, Pass pass, int len, long lines) {
         return f32 && len == 2048 && lines >= 1 << 13;
     case Pass::CONV: return 0;
     case Pass::INV_T:
-        // FP32 6.3 / 7.6 (72), 7.7 / 8.0 (528), 10.6 / 8.4 (1056), 482 / 326 (147840);
+        // FP32 6.3 / 7.6 (72), 6.8 / 7.8 (272), 10.6 / 8.4 (1056), 482 / 326 (147840);
         // FP64 7.9 / 8.1 (72), 8.8 / 8.5 (272), 188 / 161 (37056)
-        if (len == 768) return lines >= (f32 ? 1024 : 256);
+        if (len == 768) return lines >= 256;
         // 10.2 / 11.0 (272), 22.8 / 23.1 (2080), 39.0 / 37.4 (4160), 72.8 / 66.1 (8224)
         if (f32) return len == 2048 && lines >= 1 << 12;
-        // 11.6 / 10.8 (72), 13.0 / 12.8 (1056), 22.9 / 23.1 (2080), 33.6 / 35.7 (4160),
-        // 57.7 / 60.8 (9312), 101 / 85 (12352), 261 / 191 (33280)
-        return len == 1024 && (lines < 1 << 11 || lines >= 3 << 12);
+        // 11.6 / 10.8 (72), 13.0 / 12.8 (1056), 101 / 85 (12352), 261 / 191 (33280), though
+        // 33.6 / 35.7 at 4160 and 57.7 / 60.8 at 9312
+        return len == 1024;
     case Pass::C2R:
         // 1024: 13.4 / 8.0 (256 rows), 14.1 / 10.0 (1024), 25.5 / 23.2 (2304), 94 / 85
         // (9216), though 15.0 / 17.4 at 2048 and 28.0 / 32.6 at 4096, where family 0 ends

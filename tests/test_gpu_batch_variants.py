@@ -1,6 +1,6 @@
 """Batches on either side of the bounds of the untuned choices: the real passes, FP64 at
 768, change from variant 3 to 0 where the workgroups (4 rows each) no longer have a CU
-each; pass B, FP32 at 768, from family 0 to 1 at 2^10 lines and within it to variant 3
+each; pass B, FP32 at 768, from family 0 to 1 at 2^8 lines and within it to variant 3
 at 2^15.  A batch chooses by all
 its rows together and each problem by its own, and both compute the same bits."""
 import pytest
@@ -57,8 +57,8 @@ def test_batch_equals_solo_real_passes_768(F, rows, alone, batched):
 
 @pytest.mark.parametrize("Ns,alone,batched", [
     ([(64, 384, 256), (64, 384, 256)], 1, 3),    # 2 x 16448 lines
-    ([(8, 384, 12), (24, 384, 16)], 0, 0),       # 104 and 408 lines: the other family
-    ([(64, 384, 16), (8, 384, 12)], 1, 1),       # 1088 and 104: a launch for each family
+    ([(8, 384, 12), (12, 384, 8)], 0, 0),        # 104 and 108 lines: the other family
+    ([(24, 384, 16), (8, 384, 12)], 1, 1),       # 408 and 104: a launch for each family
     ([(128, 384, 256), (12, 384, 8)], 3, 3),     # 32896 lines alone
 ])
 def test_batch_equals_solo_pass_b_768(F, Ns, alone, batched):
@@ -80,8 +80,8 @@ def test_batch_equals_solo_pass_b_768(F, Ns, alone, batched):
 
 @pytest.mark.parametrize("prec,Ns,key,families", [
     ("f32", [(64, 512, 16), (256, 512, 64)], ("fwd_t", 1024), (0, 1)),   # 2^14 lines
-    ("f64", [(64, 512, 48), (8, 512, 8)], ("inv_t", 1024), (0, 1)),      # 2^11 .. 3 * 2^12
     ("f64", [(8, 384, 8), (32, 384, 16)], ("inv_t", 768), (0, 1)),       # 2^8
+    ("f32", [(8, 384, 8), (16, 384, 24)], ("inv_t", 768), (0, 1)),
     ("f32", [(48, 1024, 64), (96, 1024, 64)], ("inv_t", 2048), (0, 1)),  # 2^12
 ])
 def test_batch_of_both_families(F, prec, Ns, key, families):
